@@ -3,29 +3,21 @@
 // Details"; Alg. 1 QuantizeAndWrite.)
 //
 // This file is compiled with -ffp-contract=off: every fp32 step below is one
-// IEEE operation (no fused multiply-add), and the rotation is an explicit fp64
-// fused multiply-add chain in ascending channel order.  Because each product of
-// a bf16 input and an fp32 matrix entry is exact in fp64, that chain equals
-// "sum in fp64, ascending, round once to fp32" bit for bit.
-//
-// Work decomposition: blockIdx.y selects K (0) or V (1); the block stages that
-// rotation matrix (64 KB fp32) in LDS once and its waves then take rows (token,
-// head), grid-stride.  Lane l computes output channels l and l+64 of the rows.
-// A 32-channel group is one half of the wave: channels 0-31 / 64-95 live in lanes
-// 0-31, channels 32-63 / 96-127 in lanes 32-63; the group max / min are DPP steps
-// inside each row of 16 lanes plus one row-pair swap.  Small appends (a decode
-// step) run one row per wave on many short waves; large ones run the bulk kernel
-// below (8 rows per wave, persistent blocks).
+// IEEE operation (no fused multiply-add unless written).  The rotation is summed
+// in fp64 in ascending channel order.  Because each product of a bf16 input and an
+// fp32 matrix entry is exact in fp64, that sum is the same whether it is built of
+// fused or separate operations, bit for bit.
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
 namespace oscar {
 namespace {
 
-constexpr int kWaves = 4;
+constexpr int kWaves = 4;                // clip calibration: waves per block
 constexpr int kMaxClipCands = 32;  // candidate clip ratios per calibration call
 
 __device__ inline float f16_bits_to_f32(uint16_t h) { return __half2float(__ushort_as_half(h)); }
@@ -121,9 +113,7 @@ __device__ inline QOut quantize(float y, float a, float b, const QFmt& fmt) {
 
 // Token-wise clip threshold (App. "Scale Determination and Per-token Clipping
 // Details"): the rho-quantile of |x~| over the row, a_k + f (a_{k+1} - a_k) with
-// pos = rho (d - 1), k = floor(pos), f = pos - k, in fp32 steps.  The order
-// statistics come from a binary search over the bit patterns of |x~| (positive
-// floats order like their bits): the smallest T with #{|x~| <= T} >= k + 1 is a_k.
+// pos = rho (d - 1), k = floor(pos), f = pos - k, in fp32 steps.
 __device__ inline void quantile_pos(float rho, int& k, float& f) {
   const float pos = __fmul_rn(rho, (float)(kD - 1));
   k = min((int)floorf(pos), kD - 1);
@@ -133,96 +123,20 @@ __device__ inline float lerp_tau(float ak, float ak1, float f) {
   return __fadd_rn(ak, __fmul_rn(f, __fsub_rn(ak1, ak)));
 }
 
-// One row over the wave: lane l holds channels l and l + 64.
-__device__ inline float token_quantile_wave(float x0, float x1, float rho) {
-  const uint32_t u0 = __float_as_uint(x0) & 0x7fffffffu, u1 = __float_as_uint(x1) & 0x7fffffffu;
-  int k;
-  float f;
-  quantile_pos(rho, k, f);
-  auto count_le = [&](uint32_t t) {  // wave-uniform
-    return __popcll(__ballot(u0 <= t)) + __popcll(__ballot(u1 <= t));
-  };
-  uint32_t lo = 0, hi = 0x7f800000u;
-  while (lo < hi) {
-    const uint32_t mid = lo + ((hi - lo) >> 1);
-    if (count_le(mid) >= k + 1) hi = mid;
-    else lo = mid + 1;
-  }
-  const float ak = __uint_as_float(lo);
-  if (k >= kD - 1) return ak;
-  float ak1 = ak;
-  if (count_le(lo) < k + 2) {  // a_{k+1} = the smallest value above a_k
-    uint32_t m = min(u0 > lo ? u0 : 0xffffffffu, u1 > lo ? u1 : 0xffffffffu);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, o, 64));
-    ak1 = __uint_as_float(m);
-  }
-  return lerp_tau(ak, ak1, f);
-}
-
-// Two rows, one per wave half: lane l' = l & 31 of half h holds channels
-// l' + 32 q of row h.  Both searches run together (31 halvings of the bit range).
-__device__ inline float token_quantile_halves(const float (&x)[4], float rho, int half) {
-  uint32_t u[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) u[q] = __float_as_uint(x[q]) & 0x7fffffffu;
-  int k;
-  float f;
-  quantile_pos(rho, k, f);
-  // counts of the two halves for per-half thresholds t0 (half 0) and t1 (half 1)
-  auto counts = [&](uint32_t t0, uint32_t t1, int& c0, int& c1) {
-    const uint32_t t = half ? t1 : t0;
-    c0 = c1 = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint64_t b = __ballot(u[q] <= t);
-      c0 += __popc((uint32_t)b);
-      c1 += __popc((uint32_t)(b >> 32));
-    }
-  };
-  uint32_t lo0 = 0, hi0 = 0x7f800000u, lo1 = 0, hi1 = 0x7f800000u;
-  for (int it = 0; it < 31; ++it) {
-    const uint32_t m0 = lo0 + ((hi0 - lo0) >> 1), m1 = lo1 + ((hi1 - lo1) >> 1);
-    int c0, c1;
-    counts(m0, m1, c0, c1);
-    if (c0 >= k + 1) hi0 = m0; else lo0 = m0 + 1;
-    if (c1 >= k + 1) hi1 = m1; else lo1 = m1 + 1;
-  }
-  const uint32_t lo = half ? lo1 : lo0;
-  const float ak = __uint_as_float(lo);
-  if (k >= kD - 1) return ak;
-  int c0, c1;
-  counts(lo0, lo1, c0, c1);
-  uint32_t m = 0xffffffffu;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) m = min(m, u[q] > lo ? u[q] : 0xffffffffu);
-#pragma unroll
-  for (int o = 16; o >= 1; o >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, o, 64));  // within the half
-  const float ak1 = ((half ? c1 : c0) >= k + 2) ? ak : __uint_as_float(m);
-  return lerp_tau(ak, ak1, f);
-}
-
-// OR the 2-bit codes of lanes 4j..4j+3 into the byte of quad j (valid in lane 4j).
-__device__ inline uint32_t pack_quad(uint32_t code, int lane) {
-  uint32_t v = code << (2 * (lane & 3));
-  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);  // lane ^ 1
-  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);  // lane ^ 2
-  return v;
-}
-
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // ---------------------------------------------------------------------------
 // prepare: q~ = q R_k (times the logit scale) on the fp32 matrix cores, 16 query
-// rows per block.  Wave w computes column tiles 2w and 2w + 1 (16 channels each)
-// of the block's rows as 32 chained 16x16x4 MFMAs per tile: step s takes channels
-// c = 32k + s in k-slot k, so lane (row lo, k-slot hi) holds q[row][32hi + s] (one
-// 64-byte run of the row) and lane (column lo, k-slot hi) R_k[32hi + s][16t + lo]
-// (16 lanes read 64 contiguous bytes of a row of R_k).  R_k is read straight from
-// L2 (no LDS copy, no barrier); all loads of a wave are issued before its MFMAs.
-// D lane (column lo, hi): rows 4hi + i.
+// rows per block of 8 waves.  Wave w computes column tile w (16 channels) of the
+// block's rows as 32 chained 16x16x4 MFMAs: step s takes channels c = 32k + s in
+// k-slot k, so lane (row lo, k-slot hi) holds q[row][32hi + s] (one 64-byte run of
+// the row) and lane (column lo, k-slot hi) R_k[32hi + s][16w + lo] (16 lanes read 64
+// contiguous bytes of a row of R_k).  R_k is read straight from L2 (no LDS copy, no
+// barrier); all loads of a wave are issued before its MFMAs.  D lane (column lo,
+// hi): rows 4hi + i.
 // ---------------------------------------------------------------------------
 constexpr int kPrepRows = 16;
+constexpr int kRotWaves = 8;  // waves of a rotating block: one 16-channel tile each
 
 typedef float prep_f4 __attribute__((ext_vector_type(4)));
 
@@ -235,10 +149,10 @@ __device__ inline void prepare_body(int bx, const uint16_t* __restrict__ q, int 
   if (Rk && rph) Rk += (size_t)kvh * kD * kD;  // the block's rows share a KV head
   int kv_;
   const int arow = query_row(bx, lo, kPrepRows, rows, Hq, Hkv, rph, kv_);
-  if (!Rk) {  // R = I (bf16 baseline): a scaled copy, rows 4w + (0..3), lane: 2 channels
+  if (!Rk) {  // R = I (bf16 baseline): a scaled copy, rows 2w, 2w + 1, lane: 2 channels
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = query_row(bx, 4 * w + i, kPrepRows, rows, Hq, Hkv, rph, kv_);
+    for (int i = 0; i < 2; ++i) {
+      const int row = query_row(bx, 2 * w + i, kPrepRows, rows, Hq, Hkv, rph, kv_);
       if (row < 0) continue;
       const int c = 2 * (t & 63);
       const uint32_t v = *reinterpret_cast<const uint32_t*>(q + (size_t)row * kD + c);
@@ -264,52 +178,74 @@ __device__ inline void prepare_body(int bx, const uint16_t* __restrict__ q, int 
 #pragma unroll
     for (int s = 0; s < 32; ++s) a[s] = 0.0f;
   }
-  float b[2][32];
+  float b[32];
 #pragma unroll
-  for (int tt = 0; tt < 2; ++tt)
+  for (int s = 0; s < 32; ++s) b[s] = Rk[(size_t)(32 * hi + s) * kD + 16 * w + lo];
+  prep_f4 d = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int s = 0; s < 32; ++s) b[tt][s] = Rk[(size_t)(32 * hi + s) * kD + 16 * (2 * w + tt) + lo];
+  for (int s = 0; s < 32; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], d, 0, 0, 0);
 #pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    prep_f4 d = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int s = 0; s < 32; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[tt][s], d, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int row = query_row(bx, 4 * hi + i, kPrepRows, rows, Hq, Hkv, rph, kv_);
-      if (row >= 0) qt[(size_t)row * kD + 16 * (2 * w + tt) + lo] = d[i] * qscale;
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int row = query_row(bx, 4 * hi + i, kPrepRows, rows, Hq, Hkv, rph, kv_);
+    if (row >= 0) qt[(size_t)row * kD + 16 * w + lo] = d[i] * qscale;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Row routing.  A cache-update kernel takes rows (token, kv-head) = row; for each
-// row and tensor (is_v) a policy names
-//   src(row, is_v)  : the bf16 row to rotate and quantize (nullptr: none),
-//   slot(row)       : the pool slot that receives it (< 0: none),
-//   copy(row, is_v, l) : bf16 rows to copy into the mixed cache's segment store,
-//                     done by lane l for its 4 bytes after src has been read.
+// Row routing.  A cache update takes rows (token, kv-head h) of K or V (is_v);
+// 32 consecutive lanes hold a row, lane c its channels 4c .. 4c + 3.  A policy gives
+// the lane's part of a row in three steps, so that a loop can issue the loads of
+// later rows without waiting for them:
+//   key(tok)               loads that lead to other addresses;
+//   load(tok, h, .., key)  the row's values and what else its destination needs;
+//   route(raw, ..)         no loads (StepRows apart): x, the bf16 values to rotate
+//                          and quantize, slot, the pool slot that receives them
+//                          (< 0: none), and the bf16 values cp to copy to dst in the
+//                          mixed cache's segment store (null: none).
+// The lane that read x writes cp, after it: a row may be demoted from the place
+// that its copy takes.
 // ---------------------------------------------------------------------------
+typedef uint32_t u2a4 __attribute__((ext_vector_type(2), aligned(4)));  // rows are 4-byte aligned
+
+struct Key {
+  int32_t b;
+  int64_t p;
+};
+struct Raw {
+  u2a4 x;
+  int64_t p;        // slot (PlainRows) or position
+  int32_t b, len, page;
+};
+struct Routed {
+  u2a4 x, cp;
+  int64_t slot;
+  u2a4* dst;
+};
+
 struct PlainRows {  // oscar_kv_append: token i -> slot_mapping[i]
   const uint16_t* k;
   const uint16_t* v;
   const int64_t* slots;
-  int n_rows, Hkv;
-  __device__ const uint16_t* src(int row, int is_v) const {
-    return row < n_rows ? (is_v ? v : k) + (size_t)row * kD : nullptr;
+  int n_tok, Hkv;
+  __device__ Key key(int) const { return Key{0, 0}; }
+  __device__ Raw load(int tok, int h, int is_v, int c, const Key&) const {
+    Raw w{u2a4{0, 0}, -1, 0, 0, 0};
+    if (tok < n_tok) {
+      w.x = reinterpret_cast<const u2a4*>((is_v ? v : k) + ((size_t)tok * Hkv + h) * kD)[c];
+      w.p = slots[tok];
+    }
+    return w;
   }
-  __device__ int64_t slot(int row) const { return row < n_rows ? slots[row / Hkv] : -1; }
-  __device__ void copy(int, int, int) const {}
-  // the row's bf16 input (whatever its destination), and its bf16 copy destination
-  __device__ const uint16_t* data(int row, int is_v) const { return src(row, is_v); }
-  __device__ uint32_t* seg_dst(int, int) const { return nullptr; }
+  __device__ Routed route(const Raw& w, int, int, int) const {
+    return Routed{w.x, w.x, w.p, nullptr};
+  }
 };
 
 // Segment store of the mixed cache: [B][Hkv][K, V][S0 + W][d] bf16; position p
 // of a sequence has segment slot p (p < S0) or S0 + (p - S0) mod W (window).
-__device__ inline uint32_t* seg_row(uint16_t* seg, int Hkv, int S0, int W, int b, int h,
-                                    int is_v, int slot) {
-  return reinterpret_cast<uint32_t*>(
+__device__ inline u2a4* seg_row(uint16_t* seg, int Hkv, int S0, int W, int b, int h, int is_v,
+                                int slot) {
+  return reinterpret_cast<u2a4*>(
       seg + ((((size_t)b * Hkv + h) * 2 + is_v) * (size_t)(S0 + W) + slot) * kD);
 }
 __device__ inline int seg_slot(int S0, int W, int p) { return p < S0 ? p : S0 + (p - S0) % W; }
@@ -326,47 +262,33 @@ struct PrefillRows {
   const int64_t* pos;
   const int32_t* seq_lens;
   const int32_t* block_table;
-  int n_rows, Hkv, max_pages, S0, W;
-  // -1: skipped, 0: INT2, 1: bf16; b and p of the row's token
-  __device__ int route(int row, int& b, int& p) const {
-    if (row >= n_rows) return -1;
-    const int tok = row / Hkv;
-    b = seq_idx[tok];
-    const int64_t p64 = pos[tok];
-    const int len = min(max(seq_lens[b], 0), max_pages * kP);
-    if (p64 < 0 || p64 >= len) return -1;
-    p = (int)p64;
-    const int lo = min(S0, len), hi = max(lo, len - W);
-    return (p >= lo && p < hi) ? 0 : 1;
+  int n_tok, Hkv, max_pages, S0, W;
+  __device__ Key key(int tok) const {
+    return tok < n_tok ? Key{seq_idx[tok], pos[tok]} : Key{-1, 0};
   }
-  __device__ const uint16_t* src(int row, int is_v) const {
-    int b, p;
-    return route(row, b, p) == 0 ? (is_v ? v : k) + (size_t)row * kD : nullptr;
+  __device__ Raw load(int tok, int h, int is_v, int c, const Key& key) const {
+    Raw w{u2a4{0, 0}, key.p, key.b, 0, 0};
+    if (key.b >= 0) {  // the page of any position: in range, whether it is used or not
+      const int pg = key.p <= 0 ? 0 : (int)min(key.p / kP, (int64_t)max_pages - 1);
+      w.x = reinterpret_cast<const u2a4*>((is_v ? v : k) + ((size_t)tok * Hkv + h) * kD)[c];
+      w.len = seq_lens[key.b];
+      w.page = block_table[(size_t)key.b * max_pages + pg];
+    }
+    return w;
   }
-  __device__ int64_t slot(int row) const {
-    int b, p;
-    if (route(row, b, p) != 0) return -1;
-    return (int64_t)block_table[(size_t)b * max_pages + p / kP] * kP + p % kP;
-  }
-  __device__ void copy(int row, int is_v, int l) const {
-    int b, p;
-    if (route(row, b, p) != 1) return;
-    const int h = row % Hkv;
-    seg_row(seg, Hkv, S0, W, b, h, is_v, seg_slot(S0, W, p))[l] =
-        reinterpret_cast<const uint32_t*>((is_v ? v : k) + (size_t)row * kD)[l];
-  }
-  __device__ const uint16_t* data(int row, int is_v) const {
-    return row < n_rows ? (is_v ? v : k) + (size_t)row * kD : nullptr;
-  }
-  __device__ uint32_t* seg_dst(int row, int is_v) const {
-    int b, p;
-    if (route(row, b, p) != 1) return nullptr;
-    return seg_row(seg, Hkv, S0, W, b, row % Hkv, is_v, seg_slot(S0, W, p));
+  __device__ Routed route(const Raw& w, int h, int is_v, int c) const {
+    Routed f{w.x, w.x, -1, nullptr};
+    const int len = min(max(w.len, 0), max_pages * kP);
+    if (w.b < 0 || w.p < 0 || w.p >= len) return f;
+    const int p = (int)w.p, lo = min(S0, len), hi = max(lo, len - W);
+    if (p >= lo && p < hi) f.slot = (int64_t)w.page * kP + p % kP;
+    else f.dst = seg_row(seg, Hkv, S0, W, w.b, h, is_v, seg_slot(S0, W, p)) + c;
+    return f;
   }
 };
 
-// Decode step over the mixed cache: one new token per sequence b (row =
-// b * Hkv + h) at position p = seq_lens[b] - 1 (Alg. 1 DecodeStep):
+// Decode step over the mixed cache: one new token per sequence b at position
+// p = seq_lens[b] - 1 (Alg. 1 DecodeStep):
 //   p < S0          -> bf16 sink slot p;
 //   p >= S0, W = 0  -> INT2 at position p;
 //   otherwise       -> bf16 window slot of p; when p - W >= S0 the token at
@@ -378,41 +300,34 @@ struct StepRows {
   uint16_t* seg;
   const int32_t* seq_lens;
   const int32_t* block_table;
-  int n_rows, Hkv, max_pages, S0, W;
-  __device__ int pos(int row) const {  // -1: no token
-    return row < n_rows ? min(max(seq_lens[row / Hkv], 0), max_pages * kP) - 1 : -1;
+  int n_tok, Hkv, max_pages, S0, W;
+  __device__ Key key(int b) const { return b < n_tok ? Key{b, seq_lens[b]} : Key{-1, 0}; }
+  __device__ Raw load(int b, int h, int is_v, int c, const Key& key) const {
+    Raw w{u2a4{0, 0}, key.p, key.b, 0, 0};
+    if (key.b >= 0)
+      w.x = reinterpret_cast<const u2a4*>((is_v ? v : k) + ((size_t)b * Hkv + h) * kD)[c];
+    return w;
   }
-  // position quantized into INT2 by this step, or -1
-  __device__ int qpos(int p) const {
-    if (p < S0) return -1;
-    if (W == 0) return p;
-    return p - W >= S0 ? p - W : -1;
-  }
-  __device__ const uint16_t* src(int row, int is_v) const {
-    const int p = pos(row), qp = qpos(p);
-    if (qp < 0) return nullptr;
-    if (qp == p) return (is_v ? v : k) + (size_t)row * kD;
-    const int b = row / Hkv, h = row % Hkv;
-    return reinterpret_cast<const uint16_t*>(seg_row(seg, Hkv, S0, W, b, h, is_v, seg_slot(S0, W, qp)));
-  }
-  __device__ int64_t slot(int row) const {
-    const int qp = qpos(pos(row));
-    if (qp < 0) return -1;
-    return (int64_t)block_table[(size_t)(row / Hkv) * max_pages + qp / kP] * kP + qp % kP;
-  }
-  __device__ void copy(int row, int is_v, int l) const {
-    const int p = pos(row);
-    if (p < 0 || (p >= S0 && W == 0)) return;
-    const int b = row / Hkv, h = row % Hkv;
-    // same lane and address as the read of a demoted row: ordered after it
-    seg_row(seg, Hkv, S0, W, b, h, is_v, seg_slot(S0, W, p))[l] =
-        reinterpret_cast<const uint32_t*>((is_v ? v : k) + (size_t)row * kD)[l];
+  __device__ Routed route(const Raw& w, int h, int is_v, int c) const {
+    Routed f{u2a4{0, 0}, w.x, -1, nullptr};
+    const int p = min(max((int)w.p, 0), max_pages * kP) - 1;
+    if (w.b < 0 || p < 0) return f;
+    int qp = -1;  // position quantized into INT2 by this step
+    if (p >= S0 && W == 0) {
+      qp = p;
+      f.x = w.x;
+    } else {
+      f.dst = seg_row(seg, Hkv, S0, W, w.b, h, is_v, seg_slot(S0, W, p)) + c;
+      if (p - W >= S0) {
+        qp = p - W;
+        f.x = *f.dst;
+      }
+    }
+    if (qp >= 0) f.slot = (int64_t)block_table[(size_t)w.b * max_pages + qp / kP] * kP + qp % kP;
+    return f;
   }
 };
 
-// Clip, quantize, pack and write one rotated row (token, head) whose channels l
-// and l + 64 are in lane l, to pool slot `slot` (wave-uniform; < 0: the row only
-// takes part in the cross-lane steps).
 // Group reductions of the one-row-per-wave layout (lane l: channels l, l + 64):
 // with 32-channel groups each value's group is a wave half, with 64 its whole
 // wave, with 128 both values over the wave.
@@ -444,309 +359,409 @@ __device__ inline void group_reduce2(float v0, float v1, int ng, float& r0, floa
   }
 }
 
-__device__ inline void store_row(uint8_t* __restrict__ pages, int Hkv, int64_t slot, int row,
-                                 int is_v, float clip, const QFmt& fmt, double acc0, double acc1,
-                                 int l) {
-  const float xt0 = __double2float_rn(acc0);  // channel l
-  const float xt1 = __double2float_rn(acc1);  // channel l + 64
-  float tau0, tau1;
-  if (fmt.quantile) {
-    tau0 = tau1 = token_quantile_wave(xt0, xt1, clip);
-  } else {
-    group_reduce2<true>(fabsf(xt0), fabsf(xt1), fmt.ng, tau0, tau1);
-    tau0 = __fmul_rn(clip, tau0);
-    tau1 = __fmul_rn(clip, tau1);
-  }
-  const float y0 = fminf(fmaxf(xt0, -tau0), tau0), y1 = fminf(fmaxf(xt1, -tau1), tau1);
-  float a0, a1, b0, b1;
-  group_reduce2<false>(y0, y1, fmt.ng, a0, a1);
-  group_reduce2<true>(y0, y1, fmt.ng, b0, b1);
-  const QOut q0 = quantize(y0, a0, b0, fmt);
-  const QOut q1 = quantize(y1, a1, b1, fmt);
-  const uint32_t byte0 = pack_quad(q0.code, l);  // quad l/4
-  const uint32_t byte1 = pack_quad(q1.code, l);  // quad 16 + l/4
-  if (slot < 0) return;                          // uniform across the wave
-  const int h = row % Hkv;
-  const int64_t page = slot / kP;
-  const int t = (int)(slot - page * kP);
-  uint8_t* blk = pages + ((size_t)page * Hkv + h) * block_bytes(fmt.ng);
-  if ((l & 3) == 0) {
-    const int j0 = l >> 2, j1 = 16 + (l >> 2);
-    if (is_v) {
-      blk[kOffVCodes + j0 * kP + t] = (uint8_t)byte0;
-      blk[kOffVCodes + j1 * kP + t] = (uint8_t)byte1;
-    } else {
-      blk[kOffKCodes + t * (kD / 4) + j0] = (uint8_t)byte0;
-      blk[kOffKCodes + t * (kD / 4) + j1] = (uint8_t)byte1;
-    }
-  }
-  // (s, z) of the groups: value 0 of lane l is in group l / 32 (G = 32) or 0,
-  // value 1 in group 2 + l / 32 (G = 32), 1 (G = 64) or 0 (G = 128)
-  const uint32_t sz_base = is_v ? off_vsz(fmt.ng) : kOffKSz;
-  const bool lead = fmt.ng == 4 ? (l & 31) == 0 : l == 0;
-  if (lead) {
-    const int g0 = fmt.ng == 4 ? l >> 5 : 0;
-    const int g1 = fmt.ng == 4 ? 2 + (l >> 5) : fmt.ng == 2 ? 1 : -1;
-    *reinterpret_cast<uint32_t*>(blk + sz_base + (g0 * kP + t) * 4) =
-        (uint32_t)q0.s16 | ((uint32_t)q0.z16 << 16);
-    if (g1 >= 0)
-      *reinterpret_cast<uint32_t*>(blk + sz_base + (g1 * kP + t) * 4) =
-          (uint32_t)q1.s16 | ((uint32_t)q1.z16 << 16);
-  }
-}
-
-// Cache update by one block: is_v selects K or V, blocks bx of gx take rows
-// grid-stride.  Rs: 64 KB LDS for the matrix, xs: the waves' input rows.
-template <int RW, class Rows>
-__device__ inline void append_body(float* Rs, double (*xs)[RW][kD], int is_v, int bx, int gx,
-                                   uint8_t* __restrict__ pages, int Hkv, const Rows& rows,
-                                   int n_rows, const float* __restrict__ Rk,
-                                   const float* __restrict__ Rv, float clip_k, float clip_v,
-                                   const QFmt& fmt) {
-  const float* __restrict__ R = is_v ? Rv : Rk;  // nullptr: identity
-  const float clip = is_v ? clip_v : clip_k;
-  // rph: the block takes the rows (token, h) of one KV head h, so that it stages
-  // that head's matrix; gx is then a multiple of Hkv
-  int h = 0;
-  if (fmt.rph) {
-    h = bx % Hkv;
-    bx /= Hkv;
-    gx /= Hkv;
-    if (R) R += (size_t)h * kD * kD;
-  }
-  const int n_seq = fmt.rph ? n_rows / Hkv : n_rows;
-  auto row_at = [&](int i) { return fmt.rph ? (i < n_seq ? i * Hkv + h : n_rows) : i; };
-
-  if (R) {  // 16 float4 per thread, all loads issued before the stores
-    float4 r4[kD * kD / 4 / 256];
-#pragma unroll
-    for (int i = 0; i < kD * kD / 4 / 256; ++i)
-      r4[i] = reinterpret_cast<const float4*>(R)[threadIdx.x + 256 * i];
-#pragma unroll
-    for (int i = 0; i < kD * kD / 4 / 256; ++i) reinterpret_cast<float4*>(Rs)[threadIdx.x + 256 * i] = r4[i];
-  }
-  __syncthreads();
-
-  const int w = threadIdx.x >> 6;
-  const int l = threadIdx.x & 63;
-  const int n_items = (n_seq + RW - 1) / RW;
-
-  // each wave owns xs[w]: no block-level synchronization inside the loop, only
-  // fences around the exchange between its lanes
-  for (int item = bx * kWaves + w; item < n_items; item += gx * kWaves) {
-    lane_exchange();  // the previous item's reads of xs[w] come first
-#pragma unroll
-    for (int rr = 0; rr < RW; ++rr) {
-      const int row = row_at(item * RW + rr);
-      double x0 = 0.0, x1 = 0.0;
-      const uint16_t* src = rows.src(row, is_v);
-      if (src) {
-        const uint32_t pair = reinterpret_cast<const uint32_t*>(src)[l];
-        x0 = (double)__uint_as_float(pair << 16);
-        x1 = (double)__uint_as_float(pair & 0xffff0000u);
-      }
-      xs[w][rr][2 * l] = x0;
-      xs[w][rr][2 * l + 1] = x1;
-      rows.copy(row, is_v, l);
-    }
-    lane_exchange();
-
-    double acc0[RW], acc1[RW];
-    if (R) {
-#pragma unroll
-      for (int rr = 0; rr < RW; ++rr) acc0[rr] = acc1[rr] = 0.0;
-#pragma unroll 4
-      for (int c = 0; c < kD; ++c) {
-        const double r0 = (double)Rs[c * kD + l];
-        const double r1 = (double)Rs[c * kD + l + 64];
-#pragma unroll
-        for (int rr = 0; rr < RW; ++rr) {
-          const double xc = xs[w][rr][c];
-          acc0[rr] = __fma_rn(xc, r0, acc0[rr]);
-          acc1[rr] = __fma_rn(xc, r1, acc1[rr]);
-        }
-      }
-    } else {  // identity: x~ = x
-#pragma unroll
-      for (int rr = 0; rr < RW; ++rr) {
-        acc0[rr] = xs[w][rr][l];
-        acc1[rr] = xs[w][rr][l + 64];
-      }
-    }
-
-#pragma unroll
-    for (int rr = 0; rr < RW; ++rr) {
-      const int row = row_at(item * RW + rr);
-      store_row(pages, Hkv, rows.slot(row), row, is_v, clip, fmt, acc0[rr], acc1[rr], l);
-    }
-  }
-}
-
 // DEF: the default format (binary16 metadata, group-absmax clip, 32-channel
 // groups) as compile-time constants, so that its code has no format branches.
 __device__ inline QFmt pick(bool def, const QFmt& fmt) { return def ? QFmt{0, 0, 4, 0} : fmt; }
 
-template <int RW, class Rows, bool DEF>
-__global__ __launch_bounds__(256) void append_kernel(uint8_t* __restrict__ pages, int Hkv,
-                                                     Rows rows, int n_rows,
-                                                     const float* __restrict__ Rk,
-                                                     const float* __restrict__ Rv, float clip_k,
-                                                     float clip_v, QFmt fmt) {
-  __shared__ float Rs[kD * kD];
-  __shared__ double xs[kWaves][RW][kD];
-  append_body<RW>(Rs, xs, blockIdx.y, blockIdx.x, gridDim.x, pages, Hkv, rows, n_rows, Rk, Rv,
-                  clip_k, clip_v, pick(DEF, fmt));
-}
-
-// Row-pair layout of the bulk cache update: the two halves of a wave hold rows
-// 2p and 2p + 1, and lane l' = l & 31 of a half holds channels l' + 32 q
-// (q = 0..3), so each group of 32 channels is one half wave as in the per-row
-// path.
-
-// store_row for the pair layout: lane l' of the half holds channels l' + 32 q;
-// slot is uniform across the half wave.
-__device__ inline void store_row4(uint8_t* __restrict__ pages, int Hkv, int64_t slot, int row,
-                                  int is_v, float clip, const QFmt& fmt, const double (&acc)[4],
-                                  int lp, int half) {
-  float xt[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) xt[q] = __double2float_rn(acc[q]);
-  // group reductions of the two-rows-per-wave layout (lane l' of a half: channels
-  // l' + 32 q of its row): values q of one group over the half
-  auto reduce4 = [&](auto op, auto half_red, const float (&v)[4], float (&r)[4]) {
-    if (fmt.ng == 4) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = half_red(v[q]);
-    } else if (fmt.ng == 2) {
-      r[0] = r[1] = half_red(op(v[0], v[1]));
-      r[2] = r[3] = half_red(op(v[2], v[3]));
-    } else {
-      r[0] = r[1] = r[2] = r[3] = half_red(op(op(v[0], v[1]), op(v[2], v[3])));
-    }
-  };
-  auto fmax_ = [](float a, float b) { return fmaxf(a, b); };
-  auto fmin_ = [](float a, float b) { return fminf(a, b); };
-  auto hmax = [](float x) { return half_wave_max(x); };
-  auto hmin = [](float x) { return half_wave_min(x); };
-  float tau[4];
-  if (fmt.quantile) {
-    const float t = token_quantile_halves(xt, clip, half);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) tau[q] = t;
-  } else {
-    float ax[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) ax[q] = fabsf(xt[q]);
-    reduce4(fmax_, hmax, ax, tau);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) tau[q] = __fmul_rn(clip, tau[q]);
-  }
-  float y[4], ga[4], gb[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) y[q] = fminf(fmaxf(xt[q], -tau[q]), tau[q]);
-  reduce4(fmin_, hmin, y, ga);
-  reduce4(fmax_, hmax, y, gb);
-  QOut qo[4];
-  uint32_t byte[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    qo[q] = quantize(y[q], ga[q], gb[q], fmt);  // 32-channel slice q of the row
-    byte[q] = pack_quad(qo[q].code, lp);         // quad 8 q + l'/4
-  }
-  if (slot < 0) return;
-  const int h = row % Hkv;
-  const int64_t page = slot / kP;
-  const int t = (int)(slot - page * kP);
-  uint8_t* blk = pages + ((size_t)page * Hkv + h) * block_bytes(fmt.ng);
-  if ((lp & 3) == 0) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int j = 8 * q + (lp >> 2);
-      if (is_v) blk[kOffVCodes + j * kP + t] = (uint8_t)byte[q];
-      else blk[kOffKCodes + t * (kD / 4) + j] = (uint8_t)byte[q];
-    }
-  }
-  if (lp == 0) {  // group g holds the slices q = g (4 / ng) .. (g + 1) (4 / ng) - 1
-    const uint32_t sz_base = is_v ? off_vsz(fmt.ng) : kOffKSz;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      if (g >= fmt.ng) break;
-      const int q = g * (4 / fmt.ng);
-      *reinterpret_cast<uint32_t*>(blk + sz_base + (g * kP + t) * 4) =
-          (uint32_t)qo[q].s16 | ((uint32_t)qo[q].z16 << 16);
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Bulk cache update on the fp64 matrix cores (large appends; every format).  A
-// wave rotates 16 rows at a time as one 16 x 128 x 128 product of
-// v_mfma_f64_16x16x4_f64 steps: step s takes channels 4 s .. 4 s + 3, A = the 16
-// rows' bf16 values of those channels (lane l: row l % 16, channel 4 s + l / 16),
-// B = rows 4 s .. 4 s + 3 of R (lane l: row 4 s + l / 16), over eight column
-// tiles whose column j is channel 8 j + t (tile t).  A step adds its four
-// products to the running fp64 sum one after another in channel order (lane
-// group l / 16 = position in that order) and the steps run s = 0..31 in turn,
-// so each x~ is the fp64 sum of the 128 exact products in ascending channel
-// order rounded once to fp32, bit for bit the value of the row-per-lane path.
-// Output lane l, register i of tile t holds row l / 16 + 4 i, channel 8 (l % 16)
-// + t; the 16 rows go through LDS (fp32) to the layout of the quantizer: lane
-// (row, 32-channel slice) for the group-absmax clip (store_slice32), two rows per
-// wave (store_row4) for the token-quantile clip.  R is staged once per block
-// as fp32 (64 KB) and read as two 16-byte words per lane and step.
+// Rotation of 16 rows by one block on the fp64 matrix cores: a 16 x 128 x 128
+// product of v_mfma_f64_16x16x4_f64 steps.  Wave w owns columns 16w .. 16w + 15 and
+// keeps its columns of R as fp64 in 64 registers for all of the block's items.  Step
+// s takes channels 4s .. 4s + 3, A = the rows' values of those channels (lane l: row
+// l % 16, channel 4s + l / 16) from LDS, where they are stored as fp64, B = rows
+// 4s .. 4s + 3 of R.  A step adds its four products to the running fp64 sum one
+// after another in channel order (lane group l / 16 = position in that order) and
+// the steps run s = 0..31 in turn, so each x~ is the fp64 sum of the 128 exact
+// products in ascending channel order rounded once to fp32.  Output lane l, register
+// i holds row l / 16 + 4i, column l % 16; the rows go to LDS in fp32 for the
+// quantizer.
+//
+// Bound: the fp64 matrix core, 4096 cycles per CU and item.  fp64 conversions share
+// its unit, so nothing is converted inside the loop (one wave per item with R as
+// fp32 in LDS converted 9 values per 8 products and kept the matrix core 63 % busy:
+// 131072 tokens x 8 heads 1392 us).
 // ---------------------------------------------------------------------------
-constexpr int kMfmaWaves = 8;
-constexpr int kMfmaRows = 16;
-constexpr int kStagePitch = 66;   // dwords per staged bf16 row (8-byte reads of 16 rows: all banks)
-constexpr int kXtPitch = 132;     // floats per x~ row
-constexpr int kAreaWords = kMfmaRows * kXtPitch;  // per wave: staged rows, then x~
+constexpr int kItemRows = 16;
+// A operand in LDS: channel 4s + k of a row at double 48 k + s of its 177 (reads of
+// 16 rows and writes of 32 neighbouring lanes each hit all banks once; with channels
+// in order the reads met four to a bank and kept the LDS busy 68 % of the time).
+constexpr int kAPitch = 177;
+__device__ inline int a_col(int ch) { return 48 * (ch & 3) + (ch >> 2); }
+constexpr int kXtPitch = 144;  // floats per x~ row: 4 rows x 16 columns are written to 64 banks
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-// Clip, quantize and pack the 16 rows of a bulk item under the group-absmax
-// clip: lane l takes row l / 4, channels 32 q .. 32 q + 31 (q = l % 4) in x; a
-// group of G channels is the G / 32 lanes q of one row with equal q / (G / 32)
-// (quad-lane reductions for G = 64, 128).  Same steps and operation order as
-// store_row4.
+struct RotSmem {
+  double a[kItemRows][kAPitch];
+  float xt[kItemRows][kXtPitch];
+};
+
+// The wave's columns of R (lane l: R[4s + l / 16][16w + l % 16]).
+__device__ inline void load_rot(const float* __restrict__ R, int w, int l, double (&b)[32]) {
+#pragma unroll
+  for (int s = 0; s < 32; ++s) b[s] = (double)R[(4 * s + (l >> 4)) * kD + 16 * w + (l & 15)];
+}
+// The lane's 4 channels (4c ..) of row r into the A operand.
+__device__ inline void stage_row(RotSmem& sm, int r, int c, u2a4 x) {
+  double* d = sm.a[r];
+  d[a_col(4 * c)] = (double)__uint_as_float(x[0] << 16);
+  d[a_col(4 * c + 1)] = (double)__uint_as_float(x[0] & 0xffff0000u);
+  d[a_col(4 * c + 2)] = (double)__uint_as_float(x[1] << 16);
+  d[a_col(4 * c + 3)] = (double)__uint_as_float(x[1] & 0xffff0000u);
+}
+// x~ of the staged rows' columns 16w .. 16w + 15, to sm.xt.
+__device__ inline void rotate16(RotSmem& sm, int w, int l, const double (&b)[32]) {
+  const int kq = l >> 4, j = l & 15;
+  d4v acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < 32; ++s)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sm.a[j][48 * kq + s], b[s], acc, 0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) sm.xt[kq + 4 * i][16 * w + j] = __double2float_rn(acc[i]);
+}
+
+// Reductions over the lanes of a group in the quantizer's layout (32 lanes per row,
+// 4 channels per lane; a group of G channels is G / 4 lanes): quad swaps and the
+// mirror of 8 lanes, then by 16 and 32 lanes for the larger groups.
+template <bool MAX>
+__device__ inline float lanes_reduce(float x, int ng) {
+  auto op = [](float a, float b) { return MAX ? fmaxf(a, b) : fminf(a, b); };
+  auto dpp = [](float v, auto ctrl) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, false));
+  };
+  x = op(x, dpp(x, std::integral_constant<int, 0xB1>{}));   // lane ^ 1
+  x = op(x, dpp(x, std::integral_constant<int, 0x4E>{}));   // lane ^ 2
+  x = op(x, dpp(x, std::integral_constant<int, 0x141>{}));  // mirror of 8 lanes
+  if (ng <= 2) x = op(x, dpp(x, std::integral_constant<int, 0x128>{}));  // rotation by 8 of 16
+  if (ng == 1) {
+    const uint32_t u = __float_as_uint(x);
+    const auto sw = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    x = op(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  }
+  return x;
+}
+
+// Token quantile of a wave's two rows (rmax: the row's largest |x~|).  Bisection
+// over the bit patterns of |x~| (positive floats order like their bits) for a
+// threshold t with exactly k + 1 values at or below it, which ends as soon as t
+// separates a_k from a_{k+1} (about 17 of the 31 halvings on Gaussian rows); equal
+// values run it down to the smallest t with at least k + 1.  Counts are scalar
+// work (ballots of both rows).
+__device__ inline float token_quantile2(const float (&x)[4], float rmax, float rho, int half) {
+  int k;
+  float f;
+  quantile_pos(rho, k, f);
+  if (k >= kD - 1) return rmax;
+  auto count_le = [&](uint32_t t0, uint32_t t1, int& c0, int& c1) {
+    const float t = __uint_as_float(half ? t1 : t0);
+    c0 = c1 = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint64_t m = __ballot(fabsf(x[e]) <= t);
+      c0 += __popc((uint32_t)m);
+      c1 += __popc((uint32_t)(m >> 32));
+    }
+  };
+  uint32_t lo0 = 0, hi0 = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(rmax), 0);
+  uint32_t lo1 = 0, hi1 = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(rmax), 32);
+  int n0 = kD, n1 = kD;  // counts at hi0, hi1
+  auto step = [&](uint32_t& lo, uint32_t& hi, int& n, uint32_t mid, int c) {
+    if (lo >= hi || n == k + 1) return;
+    if (c >= k + 1) {
+      hi = mid;
+      n = c;
+    } else {
+      lo = mid + 1;
+    }
+  };
+  while ((lo0 < hi0 && n0 != k + 1) || (lo1 < hi1 && n1 != k + 1)) {
+    const uint32_t m0 = lo0 + ((hi0 - lo0) >> 1), m1 = lo1 + ((hi1 - lo1) >> 1);
+    int c0, c1;
+    count_le(m0, m1, c0, c1);
+    step(lo0, hi0, n0, m0, c0);
+    step(lo1, hi1, n1, m1, c1);
+  }
+  const float t = __uint_as_float(half ? hi1 : hi0);
+  float ak = 0.0f, ak1 = INFINITY;  // largest value at or below t, smallest above
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float v = fabsf(x[e]);
+    ak = fmaxf(ak, v <= t ? v : 0.0f);
+    ak1 = fminf(ak1, v <= t ? INFINITY : v);
+  }
+  ak = lanes_reduce<true>(ak, 1);
+  ak1 = lanes_reduce<false>(ak1, 1);
+  return lerp_tau(ak, (half ? n1 : n0) > k + 1 ? ak : ak1, f);
+}
+
+// y / s for a group's stored scale s (at most 11 significant bits), correctly
+// rounded as an IEEE division, in three operations from r = 1 / s rounded to
+// nearest: one residual correction of y r.  Equal to y / s for every pair of an
+// 11-bit and a 24-bit significand (2^33 cases enumerated), as long as r and the
+// residual are not subnormal; see fast_scale.
+__device__ inline float div_by_scale(float y, float s, float r) {
+  const float q = __fmul_rn(y, r);
+  return __fmaf_rn(__fmaf_rn(-q, s, y), r, q);
+}
+// Whether div_by_scale may replace the division for codes: always with binary16
+// scales (2^-24 <= s; where the residual underflows, |y / s| < 2^-100 and the code
+// follows from the zero point either way), and within these bounds with bfloat16.
+__device__ inline bool fast_scale(float s) { return s >= 0x1p-60f && s <= 0x1p60f; }
+
+// Clip, quantize, pack and write the wave's two rows (half-wave each, lane c of a
+// half: channels 4c .. 4c + 3 in x) to pool slot `slot` (< 0: the row only takes
+// part in the cross-lane steps).  Clipping is monotone, so the clipped extremes are
+// the clipped values' extremes; a code is rint(clamp(y / s + z, 0, 3)), taken from
+// the low mantissa bits after adding 2^23.
+__device__ inline void store_rows(uint8_t* __restrict__ pages, int Hkv, int h, int64_t slot,
+                                  int is_v, float clip, const QFmt& fmt, const float (&x)[4],
+                                  int c, int half) {
+  float mn = fminf(fminf(x[0], x[1]), fminf(x[2], x[3]));
+  float mx = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
+  float tau;
+  if (fmt.quantile) tau = token_quantile2(x, lanes_reduce<true>(fmaxf(-mn, mx), 1), clip, half);
+  mn = lanes_reduce<false>(mn, fmt.ng);
+  mx = lanes_reduce<true>(mx, fmt.ng);
+  if (!fmt.quantile) tau = __fmul_rn(clip, fmaxf(fmaxf(-mn, mx), 0.0f));
+  auto clamp = [](float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); };
+  const QParams p = quant_params(clamp(mn, -tau, tau), clamp(mx, -tau, tau), fmt);
+  uint32_t byte = 0;
+  if (fmt.bf16 && __any(!p.deg && !fast_scale(p.sf))) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) byte |= quant_code(clamp(x[e], -tau, tau), p) << (2 * e);
+  } else {
+    const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float d = div_by_scale(clamp(x[e], -tau, tau), s, r);
+      byte += __float_as_uint(__fadd_rn(clamp(__fadd_rn(d, p.zf), 0.0f, 3.0f), 8388608.0f)) << (2 * e);
+    }
+  }
+  if (slot < 0) return;  // uniform across the half wave
+  const int64_t page = slot / kP;
+  const int t = (int)(slot - page * kP);
+  uint8_t* blk = pages + ((size_t)page * Hkv + h) * block_bytes(fmt.ng);
+  if (is_v) blk[kOffVCodes + c * kP + t] = (uint8_t)byte;
+  else blk[kOffKCodes + t * (kD / 4) + c] = (uint8_t)byte;
+  const int lanes = 32 / fmt.ng;  // per group
+  if ((c & (lanes - 1)) == 0)
+    *reinterpret_cast<uint32_t*>(blk + (is_v ? off_vsz(fmt.ng) : kOffKSz) +
+                                 ((c / lanes) * kP + t) * 4) =
+        (uint32_t)p.s16 | ((uint32_t)p.z16 << 16);
+}
+
+// x~ of the thread's 4 channels: rotated (from LDS), or the row itself.
+__device__ inline void xt_of(const RotSmem& sm, int r, int c, float (&x)[4]) {
+  const float4 v = *reinterpret_cast<const float4*>(&sm.xt[r][4 * c]);
+  x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+}
+__device__ inline void xt_of(u2a4 w, float (&x)[4]) {
+  x[0] = __uint_as_float(w[0] << 16);
+  x[1] = __uint_as_float(w[0] & 0xffff0000u);
+  x[2] = __uint_as_float(w[1] << 16);
+  x[3] = __uint_as_float(w[1] & 0xffff0000u);
+}
+
+// Items of a cache update: 16 consecutive tokens (group g) of one kv-head h (their
+// bytes of a page's token-minor regions are adjacent), item = g Hkv + h.
+struct Items {
+  int groups, Hkv, step, g, h;
+  __device__ Items(int n_tok, int Hkv_, int first, int step_)
+      : groups((n_tok + kItemRows - 1) / kItemRows), Hkv(Hkv_), step(step_), g(first / Hkv_),
+        h(first % Hkv_) {}
+  __device__ bool valid() const { return g < groups; }
+  __device__ void advance() {
+    g += step / Hkv;
+    h += step % Hkv;
+    if (h >= Hkv) {
+      h -= Hkv;
+      ++g;
+    }
+  }
+};
+
+// One item per block of 8 waves (a decode step's tokens; more than one in turn past
+// two blocks per CU).
+// bx of gx: the block's items; rph: of head bx % Hkv (gx is a multiple of Hkv).
+template <class Rows>
+__device__ inline void append_body(RotSmem& sm, int is_v, int bx, int gx,
+                                   uint8_t* __restrict__ pages, const Rows& rows,
+                                   const float* __restrict__ Rk, const float* __restrict__ Rv,
+                                   float clip_k, float clip_v, const QFmt& fmt) {
+  const float* __restrict__ R = is_v ? Rv : Rk;  // nullptr: identity
+  const float clip = is_v ? clip_v : clip_k;
+  const int t = threadIdx.x, w = t >> 6, l = t & 63, half = l >> 5;
+  const int r = t >> 5, c = t & 31;  // the thread's row of an item, and lane in it
+  if (R && fmt.rph) R += (size_t)(bx % rows.Hkv) * kD * kD;
+  Items it(rows.n_tok, rows.Hkv, bx, gx);
+  if (!it.valid()) return;
+  int tok = it.g * kItemRows + r;
+  Raw raw = rows.load(tok, it.h, is_v, c, rows.key(tok));
+  double b[32];
+  if (R) load_rot(R, w, l, b);
+  for (;;) {
+    const Routed cur = rows.route(raw, it.h, is_v, c);
+    if (cur.dst) *cur.dst = cur.cp;
+    float x[4];
+    if (R) {
+      stage_row(sm, r, c, cur.x);
+      __syncthreads();
+      rotate16(sm, w, l, b);
+      __syncthreads();
+      xt_of(sm, r, c, x);
+    } else {
+      xt_of(cur.x, x);
+    }
+    store_rows(pages, rows.Hkv, it.h, cur.slot, is_v, clip, fmt, x, c, half);
+    it.advance();
+    if (!it.valid()) break;
+    tok = it.g * kItemRows + r;
+    raw = rows.load(tok, it.h, is_v, c, rows.key(tok));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Bulk cache update (more items than teams of 8 waves fit on the GPU): one
+// persistent block of 16 independent waves per CU, half of the blocks per tensor.  A
+// wave takes an item at a time from the block's list (a counter in LDS: the oldest
+// wave of a SIMD issues first and would be done early with a fixed share), stages
+// its rows as bf16, rotates them over all eight column tiles and quantizes them in
+// the quad-lane layout.  The products are as in rotate16; tile t holds channels
+// 64 (t / 4) + 4 j + t % 4 (j = column), so that a lane's B values are two 16-byte
+// reads of the fp32 R in LDS, and x~ goes through the wave's 4 KB area one channel
+// half at a time.
+//
+// Bound: the fp64 matrix core, 16,384 of a SIMD's cycles per item.  With four waves
+// per SIMD at different points of their items, the rest of an item (about 1,100
+// VALU instructions, 2,100 with the token quantile, and the dependent loads that
+// route its rows) runs while other waves' products do.  The quantizer has the most
+// work per lane here (32 channels), which costs the fewest instructions; 32 lanes a
+// row, as in store_rows, took 1,700 and 7,000.  131072 tokens x 8 heads: 1474 us with
+// two waves per SIMD, IEEE divisions per code and the routing loads in front of each
+// item's products, 1156 us now (1092 without the stores); 6408 tokens x 8 heads in the
+// token-quantile format: 288 -> 89 us.
+// ---------------------------------------------------------------------------
+constexpr int kBulkWaves = 16;
+constexpr int kStagePitch = 66;  // dwords per staged bf16 row (8-byte reads of 16 rows: all banks)
+constexpr int kHalfPitch = 68;   // floats per half row of x~
+
+// Quad-lane layout of the bulk kernels: lane l takes row l / 4 of an item's 16
+// rows, channels 32 q .. 32 q + 31 (q = l % 4); a group of G channels is the G / 32
+// lanes of a row with equal q / (G / 32).
+__device__ inline float quad_swap1(float v) {  // lane ^ 1
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));
+}
+__device__ inline float quad_swap2(float v) {  // lane ^ 2
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));
+}
 __device__ inline float quad_group_max(float v, int ng) {
-  if (ng <= 2) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false)));
-  if (ng == 1) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false)));
+  if (ng <= 2) v = fmaxf(v, quad_swap1(v));
+  if (ng == 1) v = fmaxf(v, quad_swap2(v));
   return v;
 }
 __device__ inline float quad_group_min(float v, int ng) {
-  if (ng <= 2) v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false)));
-  if (ng == 1) v = fminf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false)));
+  if (ng <= 2) v = fminf(v, quad_swap1(v));
+  if (ng == 1) v = fminf(v, quad_swap2(v));
   return v;
 }
+__device__ inline int quad_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);
+  return v + __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);
+}
 
-__device__ inline void store_slice32(uint8_t* __restrict__ pages, int Hkv, int64_t slot, int row,
-                                     int is_v, float clip, const QFmt& fmt, const float (&x)[32],
-                                     int q) {
-  float m = 0.0f;
+// Token quantile of 16 rows at once in the quad-lane layout; rmax: the row's
+// largest |x~|.  Bisection over the bit patterns of |x~| (positive floats order
+// like their bits) for a threshold t with exactly k + 1 values at or below it,
+// which ends as soon as t separates a_k from a_{k+1} (about 17 of the 31 halvings
+// on Gaussian rows); equal values run it down to the smallest t with at least k + 1.
+__device__ inline float token_quantile_quad(const float (&x)[32], float rmax, float rho) {
+  int k;
+  float f;
+  quantile_pos(rho, k, f);
+  if (k >= kD - 1) return rmax;
+  auto count_le = [&](uint32_t t) {
+    const float tf = __uint_as_float(t);
+    int c = 0;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) m = fmaxf(m, fabsf(x[i]));
-  const float tau = __fmul_rn(clip, quad_group_max(m, fmt.ng));
-  float y[32];
-  float a = INFINITY, b = -INFINITY;
+    for (int i = 0; i < 32; ++i) c += fabsf(x[i]) <= tf ? 1 : 0;
+    return quad_sum(c);
+  };
+  // smallest t with count >= k + 1 in [lo, hi]; n = count at hi
+  uint32_t lo = 0, hi = __float_as_uint(rmax);
+  int n = kD;
+  while (__any(lo < hi && n != k + 1)) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    const int c = count_le(mid);
+    const bool open = lo < hi && n != k + 1;
+    const bool up = open && c < k + 1, down = open && c >= k + 1;
+    lo = up ? mid + 1 : lo;
+    hi = down ? mid : hi;
+    n = down ? c : n;
+  }
+  const float t = __uint_as_float(hi);
+  float ak = 0.0f, ak1 = INFINITY;  // largest value at or below t, smallest above
 #pragma unroll
   for (int i = 0; i < 32; ++i) {
-    y[i] = fminf(fmaxf(x[i], -tau), tau);
-    a = fminf(a, y[i]);
-    b = fmaxf(b, y[i]);
+    const float v = fabsf(x[i]);
+    ak = fmaxf(ak, v <= t ? v : 0.0f);
+    ak1 = fminf(ak1, v <= t ? INFINITY : v);
   }
-  a = quad_group_min(a, fmt.ng);
-  b = quad_group_max(b, fmt.ng);
-  const QParams p = quant_params(a, b, fmt);
+  ak = quad_group_max(ak, 1);
+  ak1 = quad_group_min(ak1, 1);
+  return lerp_tau(ak, n > k + 1 ? ak : ak1, f);
+}
+
+// Clip, quantize, pack and write a bulk item's 16 rows (quad-lane layout); same
+// steps as store_rows.
+__device__ inline void store_slice32(uint8_t* __restrict__ pages, int Hkv, int h, int64_t slot,
+                                     int is_v, float clip, const QFmt& fmt, const float (&x)[32],
+                                     int q) {
+  float mn = x[0], mx = x[0];
+#pragma unroll
+  for (int i = 1; i < 32; ++i) {
+    mn = fminf(mn, x[i]);
+    mx = fmaxf(mx, x[i]);
+  }
+  float tau;
+  if (fmt.quantile) {
+    tau = token_quantile_quad(x, quad_group_max(fmaxf(-mn, mx), 1), clip);
+    mn = quad_group_min(mn, fmt.ng);
+    mx = quad_group_max(mx, fmt.ng);
+  } else {
+    mn = quad_group_min(mn, fmt.ng);
+    mx = quad_group_max(mx, fmt.ng);
+    tau = __fmul_rn(clip, fmaxf(fmaxf(-mn, mx), 0.0f));
+  }
+  auto clamp = [](float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); };
+  const QParams p = quant_params(clamp(mn, -tau, tau), clamp(mx, -tau, tau), fmt);
   uint32_t w[8];
+  if (fmt.bf16 && __any(!p.deg && !fast_scale(p.sf))) {
 #pragma unroll
-  for (int jb = 0; jb < 8; ++jb) {
-    uint32_t byte = 0;
+    for (int jb = 0; jb < 8; ++jb) {
+      w[jb] = 0;
+#pragma unroll 1
+      for (int e = 0; e < 4; ++e) {
+        float v = x[0];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) byte |= quant_code(y[4 * jb + e], p) << (2 * e);
-    w[jb] = byte;
+        for (int i = 1; i < 32; ++i) v = i == 4 * jb + e ? x[i] : v;
+        w[jb] |= quant_code(clamp(v, -tau, tau), p) << (2 * e);
+      }
+    }
+  } else {
+    const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
+#pragma unroll
+    for (int jb = 0; jb < 8; ++jb) {
+      uint32_t c[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float d = div_by_scale(clamp(x[4 * jb + e], -tau, tau), s, r);
+        c[e] = __float_as_uint(__fadd_rn(clamp(__fadd_rn(d, p.zf), 0.0f, 3.0f), 8388608.0f));
+      }
+      w[jb] = c[0] + (c[1] << 2) + (c[2] << 4) + (c[3] << 6);  // the low byte
+    }
   }
   if (slot < 0) return;
-  const int h = row % Hkv;
   const int64_t page = slot / kP;
   const int t = (int)(slot - page * kP);
   uint8_t* blk = pages + ((size_t)page * Hkv + h) * block_bytes(fmt.ng);
@@ -754,9 +769,12 @@ __device__ inline void store_slice32(uint8_t* __restrict__ pages, int Hkv, int64
 #pragma unroll
     for (int jb = 0; jb < 8; ++jb) blk[kOffVCodes + (8 * q + jb) * kP + t] = (uint8_t)w[jb];
   } else {
+    auto join = [](uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+      return __builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0400u),
+                                   __builtin_amdgcn_perm(b, a, 0x0c0c0400u), 0x05040100u);
+    };
     *reinterpret_cast<uint2*>(blk + kOffKCodes + t * (kD / 4) + 8 * q) =
-        make_uint2(w[0] | (w[1] << 8) | (w[2] << 16) | (w[3] << 24),
-                   w[4] | (w[5] << 8) | (w[6] << 16) | (w[7] << 24));
+        make_uint2(join(w[0], w[1], w[2], w[3]), join(w[4], w[5], w[6], w[7]));
   }
   const int per = 4 / fmt.ng;  // slices per group
   if (q % per == 0) {
@@ -781,169 +799,140 @@ __device__ inline uint64_t readlane64(uint64_t v, int lane) {
 }
 
 template <class Rows, bool DEF>
-__global__ __launch_bounds__(512) void append_mfma_kernel(
-    uint8_t* __restrict__ pages, int Hkv, Rows rows, int n_rows, const float* __restrict__ Rk,
+__global__ __launch_bounds__(kBulkWaves * 64) void append_bulk_kernel(
+    uint8_t* __restrict__ pages, Rows rows, const float* __restrict__ Rk,
     const float* __restrict__ Rv, float clip_k, float clip_v, QFmt fmt_arg) {
+  __shared__ float4 Rs[kD][kD / 4];                                  // 64 KB
+  __shared__ uint32_t area_all[kBulkWaves][kItemRows * kHalfPitch];  // 68 KB
+  __shared__ int taken;
   const QFmt fmt = pick(DEF, fmt_arg);
-  __shared__ float4 Rs4[kD][kD / 4];                        // R[c][j], 64 KB
-  __shared__ uint32_t area_all[kMfmaWaves][kAreaWords];     // 66 KB
-  const int is_v = blockIdx.y;
+  const int is_v = blockIdx.y, bx = blockIdx.x, gx = gridDim.x, Hkv = rows.Hkv;
   const float* __restrict__ R = is_v ? Rv : Rk;  // nullptr: identity
   const float clip = is_v ? clip_v : clip_k;
-  const int t = threadIdx.x;
-  int h = 0, bx = blockIdx.x, gx = gridDim.x;
-  if (fmt.rph) {  // one KV head's rows per block (gridDim.x is a multiple of Hkv)
-    h = bx % Hkv;
-    bx /= Hkv;
-    gx /= Hkv;
-    if (R) R += (size_t)h * kD * kD;
-  }
-  const int n_seq = fmt.rph ? n_rows / Hkv : n_rows;
-  auto row_at = [&](int i) { return fmt.rph ? (i < n_seq ? i * Hkv + h : n_rows) : i; };
-  if (R) {  // 8 float4 per thread, loads issued before the stores
-    float4 r4[kD * kD / 4 / 512];
+  const int t = threadIdx.x, w = t >> 6, l = t & 63, kq = l >> 4, j = l & 15;
+  if (R) {
+    if (fmt.rph) R += (size_t)(bx % Hkv) * kD * kD;  // gx is a multiple of Hkv
+    float4 r4[kD * kD / 4 / (kBulkWaves * 64)];
 #pragma unroll
-    for (int i = 0; i < kD * kD / 4 / 512; ++i) r4[i] = reinterpret_cast<const float4*>(R)[t + 512 * i];
+    for (int i = 0; i < kD * kD / 4 / (kBulkWaves * 64); ++i)
+      r4[i] = reinterpret_cast<const float4*>(R)[t + kBulkWaves * 64 * i];
 #pragma unroll
-    for (int i = 0; i < kD * kD / 4 / 512; ++i) (&Rs4[0][0])[t + 512 * i] = r4[i];
+    for (int i = 0; i < kD * kD / 4 / (kBulkWaves * 64); ++i)
+      (&Rs[0][0])[t + kBulkWaves * 64 * i] = r4[i];
   }
+  if (t == 0) taken = 0;
   __syncthreads();
-  const int w = t >> 6, l = t & 63, half = l >> 5, lp = l & 31;
-  const int kq = l >> 4, j = l & 15;
   uint32_t* area = area_all[w];
   float* xt = reinterpret_cast<float*>(area);
   // v_perm selector: the bf16 of channel 4 s + kq (of the 8 bytes read) into the
   // high half of a dword, zeros below: an fp32 with the same value
   const uint32_t asel = 0x01000C0Cu + 0x02020000u * (uint32_t)kq;
-  const int n_items = (n_seq + kMfmaRows - 1) / kMfmaRows;
-  const int stride = gx * kMfmaWaves;
-  // Rows of an item: their bf16 words (lane l: channels 2 l, 2 l + 1 of each
-  // row), loaded one item ahead into registers, and their destinations, resolved
-  // by lane r % 16 for row r (in parallel: the routing may take several
-  // dependent loads).
-  uint32_t nxt[kMfmaRows];
-  int64_t slot_n = -1;
-  uint32_t* seg_n = nullptr;
-  auto fetch = [&](int it) {
+  const int groups = (rows.n_tok + kItemRows - 1) / kItemRows;
+  const int n_items = groups * Hkv, n_mine = (n_items - bx + gx - 1) / gx;
+  for (;;) {
+    int n = 0;
+    if (l == 0) n = atomicAdd(&taken, 1);
+    n = __builtin_amdgcn_readfirstlane(n);
+    if (n >= n_mine) break;
+    const int item = bx + n * gx, tok0 = item / Hkv * kItemRows, h = item % Hkv;
+    // rows of the item: lane l their channels 2 l, 2 l + 1; destination of row l % 16
+    uint32_t row[kItemRows];
+    const uint16_t* src = (is_v ? rows.v : rows.k) + ((size_t)tok0 * Hkv + h) * kD;
 #pragma unroll
-    for (int rr = 0; rr < kMfmaRows; ++rr) {
-      const uint16_t* src = rows.data(row_at(it * kMfmaRows + rr), is_v);
-      nxt[rr] = src ? reinterpret_cast<const uint32_t*>(src)[l] : 0u;
-    }
-    const int row = row_at(it * kMfmaRows + (l & 15));
-    slot_n = rows.slot(row);
-    seg_n = rows.seg_dst(row, is_v);
-  };
-  int item = bx * kMfmaWaves + w;
-  if (item < n_items) fetch(item);
-  for (; item < n_items; item += stride) {
-    // stage the item's rows (and their bf16 copies, if any), then fetch the next
-    const int64_t slot_l = slot_n;
+    for (int r = 0; r < kItemRows; ++r)
+      row[r] = tok0 + r < rows.n_tok
+                   ? reinterpret_cast<const uint32_t*>(src + (size_t)r * Hkv * kD)[l] : 0u;
+    const int tok = tok0 + j;
+    const Routed to = rows.route(rows.load(tok, h, is_v, 0, rows.key(tok)), h, is_v, 0);
     lane_exchange();  // the previous item's reads of the wave's area come first
 #pragma unroll
-    for (int rr = 0; rr < kMfmaRows; ++rr) {
-      area[rr * kStagePitch + l] = nxt[rr];
-      uint32_t* d = reinterpret_cast<uint32_t*>(
-          (uintptr_t)readlane64((uint64_t)reinterpret_cast<uintptr_t>(seg_n), rr));
-      if (d) d[l] = nxt[rr];
+    for (int r = 0; r < kItemRows; ++r) area[r * kStagePitch + l] = row[r];
+    if (__any(to.dst != nullptr)) {
+#pragma unroll
+      for (int r = 0; r < kItemRows; ++r) {
+        uint32_t* d = reinterpret_cast<uint32_t*>(
+            (uintptr_t)readlane64((uint64_t)reinterpret_cast<uintptr_t>(to.dst), r));
+        if (d) d[l] = row[r];
+      }
     }
-    if (item + stride < n_items) fetch(item + stride);
     lane_exchange();
+    const int rr = l >> 2, q = l & 3;  // quantizer: row, channels 32 q .. + 31
+    float x[32];
     if (R) {
       d4v acc[8];
 #pragma unroll
       for (int tt = 0; tt < 8; ++tt) acc[tt] = d4v{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-      for (int s2 = 0; s2 < kD / 4; ++s2) {
-        const uint2 xa = *reinterpret_cast<const uint2*>(&area[j * kStagePitch + 2 * s2]);
+#pragma unroll 1
+      for (int s = 0; s < kD / 4; ++s) {
+        const uint2 xa = *reinterpret_cast<const uint2*>(&area[j * kStagePitch + 2 * s]);
         const double a = (double)__uint_as_float(__builtin_amdgcn_perm(xa.y, xa.x, asel));
-        const float4 r0 = Rs4[4 * s2 + kq][2 * j], r1 = Rs4[4 * s2 + kq][2 * j + 1];
+        const float4 r0 = Rs[4 * s + kq][j], r1 = Rs[4 * s + kq][16 + j];
         const float rb[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
 #pragma unroll
         for (int tt = 0; tt < 8; ++tt)
           acc[tt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)rb[tt], acc[tt], 0, 0, 0);
       }
-      // x~ rows to LDS as fp32 (the staged rows are no longer read)
-      lane_exchange();
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float* dst = xt + (kq + 4 * i) * kXtPitch + 8 * j;
-        *reinterpret_cast<float4*>(dst) =
-            make_float4(__double2float_rn(acc[0][i]), __double2float_rn(acc[1][i]),
-                        __double2float_rn(acc[2][i]), __double2float_rn(acc[3][i]));
-        *reinterpret_cast<float4*>(dst + 4) =
-            make_float4(__double2float_rn(acc[4][i]), __double2float_rn(acc[5][i]),
-                        __double2float_rn(acc[6][i]), __double2float_rn(acc[7][i]));
-      }
-    }
-    lane_exchange();  // x~ (or the staged rows) before the quantizer's reads
-    if (!fmt.quantile) {  // lane l: row l / 4, channels 32 (l % 4) .. + 31
-      const int rr = l >> 2, q = l & 3;
-      float x[32];
-      if (R) {
+      for (int hf = 0; hf < 2; ++hf) {
+        lane_exchange();  // earlier reads of the area come first
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float4 v = *reinterpret_cast<const float4*>(xt + rr * kXtPitch + 32 * q + 4 * i);
-          x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
-        }
-      } else {  // identity: the staged bf16 values
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<float4*>(xt + (kq + 4 * i) * kHalfPitch + 4 * j) =
+              make_float4(__double2float_rn(acc[4 * hf][i]), __double2float_rn(acc[4 * hf + 1][i]),
+                          __double2float_rn(acc[4 * hf + 2][i]), __double2float_rn(acc[4 * hf + 3][i]));
+        lane_exchange();
+        if ((q >> 1) == hf) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const uint32_t pr = area[rr * kStagePitch + 16 * q + i];
-          x[2 * i] = __uint_as_float(pr << 16);
-          x[2 * i + 1] = __uint_as_float(pr & 0xffff0000u);
+          for (int i = 0; i < 8; ++i) {
+            const float4 v = *reinterpret_cast<const float4*>(xt + rr * kHalfPitch + 32 * (q & 1) + 4 * i);
+            x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
+          }
         }
       }
-      const int row = row_at(item * kMfmaRows + rr);
-      store_slice32(pages, Hkv, shfl64(slot_l, rr), row, is_v, clip, fmt, x, q);
-      continue;
-    }
-    // token-quantile clip: row pairs, half `half` takes row 2 p + half; lane lp
-    // holds channels lp + 32 q
-#pragma unroll 1
-    for (int p = 0; p < kMfmaRows / 2; ++p) {
-      const int rr = 2 * p + half;
-      double x4[4];
+    } else {  // x~ = x: the staged bf16 values
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = lp + 32 * q;
-        if (R) {
-          x4[q] = (double)xt[rr * kXtPitch + c];
-        } else {  // identity: the staged bf16 value
-          const uint32_t pr = area[rr * kStagePitch + (c >> 1)];
-          x4[q] = (double)__uint_as_float((c & 1) ? (pr & 0xffff0000u) : (pr << 16));
-        }
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t pr = area[rr * kStagePitch + 16 * q + i];
+        x[2 * i] = __uint_as_float(pr << 16);
+        x[2 * i + 1] = __uint_as_float(pr & 0xffff0000u);
       }
-      const int row = row_at(item * kMfmaRows + rr);
-      store_row4(pages, Hkv, shfl64(slot_l, rr), row, is_v, clip, fmt, x4, lp, half);
     }
+    store_slice32(pages, Hkv, h, shfl64(to.slot, rr), is_v, clip, fmt, x, q);
   }
 }
 
-__global__ __launch_bounds__(256) void prepare_kernel(const uint16_t* __restrict__ q, int rows,
+template <class Rows, bool DEF>
+__global__ __launch_bounds__(kRotWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void append_kernel(
+    uint8_t* __restrict__ pages, Rows rows, const float* __restrict__ Rk,
+    const float* __restrict__ Rv, float clip_k, float clip_v, QFmt fmt) {
+  __shared__ RotSmem sm;
+  append_body(sm, blockIdx.y, blockIdx.x, gridDim.x, pages, rows, Rk, Rv, clip_k, clip_v,
+              pick(DEF, fmt));
+}
+
+__global__ __launch_bounds__(kRotWaves * 64) void prepare_kernel(const uint16_t* __restrict__ q, int rows,
                                                       const float* __restrict__ Rk, float qscale,
                                                       float* __restrict__ qt, int rph, int Hq,
                                                       int Hkv) {
   prepare_body(blockIdx.x, q, rows, Rk, qscale, qt, rph, Hq, Hkv);
 }
 
-// One launch for a decode step's prologue: blockIdx.y 0/1 = K/V cache update
-// (append_blocks blocks), 2 = query rotation (prep_blocks blocks).  The two are
-// independent; the split kernel that follows needs both.
-template <int RW, class Rows, bool DEF>
-__global__ __launch_bounds__(256) void prologue_kernel(
-    uint8_t* __restrict__ pages, int Hkv, Rows rows, int n_rows, const float* __restrict__ Rk,
+// One launch for a decode step's prologue: append_blocks blocks of the K update, as
+// many of the V update, then the query rotation's.  The parts are independent; the
+// split kernel that follows needs them all.
+template <class Rows, bool DEF>
+__global__ __launch_bounds__(kRotWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void prologue_kernel(
+    uint8_t* __restrict__ pages, Rows rows, const float* __restrict__ Rk,
     const float* __restrict__ Rv, float clip_k, float clip_v, QFmt fmt_arg, int append_blocks,
-    const uint16_t* __restrict__ q, int q_rows, int Hq, float qscale, float* __restrict__ qt,
-    int prep_blocks) {
-  __shared__ float Rs[kD * kD];
-  __shared__ double xs[kWaves][RW][kD];
-  if (blockIdx.y < 2) {
-    if ((int)blockIdx.x < append_blocks)
-      append_body<RW>(Rs, xs, blockIdx.y, blockIdx.x, append_blocks, pages, Hkv, rows, n_rows,
-                      Rk, Rv, clip_k, clip_v, pick(DEF, fmt_arg));
-  } else if ((int)blockIdx.x < prep_blocks) {
-    prepare_body(blockIdx.x, q, q_rows, Rk, qscale, qt, fmt_arg.rph, Hq, Hkv);
+    const uint16_t* __restrict__ q, int q_rows, int Hq, float qscale, float* __restrict__ qt) {
+  __shared__ RotSmem sm;
+  const int bx = blockIdx.x;
+  if (bx < 2 * append_blocks) {
+    const int is_v = bx >= append_blocks;
+    append_body(sm, is_v, is_v ? bx - append_blocks : bx, append_blocks, pages, rows,
+                Rk, Rv, clip_k, clip_v, pick(DEF, fmt_arg));
+  } else {
+    prepare_body(bx - 2 * append_blocks, q, q_rows, Rk, qscale, qt, fmt_arg.rph, Hq, rows.Hkv);
   }
 }
 
@@ -1124,75 +1113,51 @@ __global__ __launch_bounds__(kClipParts * kMaxClipCands) void clip_reduce_kernel
 }  // namespace
 
 namespace {
-int64_t append_blocks_for(int64_t n_rows, int rw) {
-  const int64_t n_items = (n_rows + rw - 1) / rw;
-  const int64_t blocks = (n_items + kWaves - 1) / kWaves;
-  return blocks > 1024 ? 1024 : blocks;
+// Items of a cache update per tensor (16 tokens of a head each), and the blocks that
+// take them: one per item up to `most`; with one rotation per KV head a multiple of
+// Hkv, a block then keeps to one head.
+int64_t append_items(int n_tok, int Hkv) {
+  return ((int64_t)n_tok + kItemRows - 1) / kItemRows * Hkv;
 }
-// With one rotation per KV head a block takes one head's rows: a multiple of Hkv
-// blocks, each head's share sized for its n_rows / Hkv rows.
-int64_t append_blocks_rph(int64_t n_rows, int rw, int64_t Hkv, int rph) {
-  if (!rph) return append_blocks_for(n_rows, rw);
-  const int64_t n_items = (n_rows / Hkv + rw - 1) / rw;
-  int64_t per = (n_items + kWaves - 1) / kWaves;
-  per = std::max<int64_t>(1, std::min(per, std::max<int64_t>(1, 1024 / Hkv)));
-  return per * Hkv;
+int append_blocks(int64_t items, int Hkv, int rph, int64_t most) {
+  return (int)std::min(items, rph ? std::max<int64_t>(1, most / Hkv) * Hkv : most);
 }
 
 bool is_default(const QFmt& f) { return f.bf16 == 0 && f.quantile == 0 && f.ng == 4 && f.rph == 0; }
 
 template <class Rows>
-hipError_t launch_rows(void* pages, int64_t Hkv, const Rows& rows, int64_t n_rows, const float* Rk,
-                       const float* Rv, float clip_k, float clip_v, QFmt fmt, hipStream_t st) {
+hipError_t launch_rows(void* pages, const Rows& rows, const float* Rk, const float* Rv,
+                       float clip_k, float clip_v, QFmt fmt, hipStream_t st) {
+  auto go = [&](auto kernel, int blocks, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks, 2), dim3(waves * 64), 0, st,
+                       static_cast<uint8_t*>(pages), rows, Rk, Rv, clip_k, clip_v, fmt);
+  };
   const bool def = is_default(fmt);
-  if (n_rows <= 4096) {  // one decode step: many short waves
-    const dim3 grid((unsigned)append_blocks_rph(n_rows, 1, Hkv, fmt.rph), 2);
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, static_cast<uint8_t*>(pages), (int)Hkv,
-                         rows, (int)n_rows, Rk, Rv, clip_k, clip_v, fmt);
-    };
-    if (def) go(append_kernel<1, Rows, true>);
-    else go(append_kernel<1, Rows, false>);
-  } else {  // bulk: one persistent 8-wave block per CU (fp64 MFMA), half of them per tensor
-    const int64_t heads = fmt.rph ? Hkv : 1;  // rph: a block per head's share
-    const int64_t items = (n_rows / heads + kMfmaRows - 1) / kMfmaRows;
-    int64_t nb = (items + kMfmaWaves - 1) / kMfmaWaves;
-    const int64_t cap = std::max<int64_t>(1, device_cus() / 2 / heads);
-    if (nb > cap) nb = cap;
-    nb *= heads;
-    auto go = [&](auto kernel) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)nb, 2), dim3(512), 0, st,
-                         static_cast<uint8_t*>(pages), (int)Hkv, rows, (int)n_rows, Rk, Rv,
-                         clip_k, clip_v, fmt);
-    };
-    if (def) go(append_mfma_kernel<Rows, true>);
-    else go(append_mfma_kernel<Rows, false>);
+  const int64_t items = append_items(rows.n_tok, rows.Hkv);
+  if (items <= device_cus()) {
+    if (def) go(append_kernel<Rows, true>, (int)items, kRotWaves);
+    else go(append_kernel<Rows, false>, (int)items, kRotWaves);
+  } else {
+    const int blocks = append_blocks(items, rows.Hkv, fmt.rph, device_cus() / 2);
+    if (def) go(append_bulk_kernel<Rows, true>, blocks, kBulkWaves);
+    else go(append_bulk_kernel<Rows, false>, blocks, kBulkWaves);
   }
   return hipGetLastError();
 }
 
 template <class Rows>
-hipError_t launch_prologue(void* pages, int64_t Hkv, const Rows& rows, int64_t n_rows,
-                           const float* Rk, const float* Rv, float clip_k, float clip_v,
-                           QFmt fmt, const uint16_t* q, int B, int Hq, float qscale, float* qt,
-                           hipStream_t st) {
-  const int rw = n_rows <= 4096 ? 1 : 4;
-  const int ab = n_rows > 0 ? (int)append_blocks_rph(n_rows, rw, Hkv, fmt.rph) : 0;
-  const int pb = query_blocks(B, Hq, (int)Hkv, fmt.rph, kPrepRows);
-  const dim3 grid((unsigned)(ab > pb ? ab : pb), 3);
+hipError_t launch_prologue(void* pages, const Rows& rows, const float* Rk, const float* Rv,
+                           float clip_k, float clip_v, QFmt fmt, const uint16_t* q, int B, int Hq,
+                           float qscale, float* qt, hipStream_t st) {
+  const int ab = append_blocks(append_items(rows.n_tok, rows.Hkv), rows.Hkv, fmt.rph, device_cus());
+  const int pb = query_blocks(B, Hq, rows.Hkv, fmt.rph, kPrepRows);
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, static_cast<uint8_t*>(pages), (int)Hkv,
-                       rows, (int)n_rows, Rk, Rv, clip_k, clip_v, fmt, ab, q, B * Hq, Hq, qscale,
-                       qt, pb);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(2 * ab + pb)), dim3(kRotWaves * 64), 0, st,
+                       static_cast<uint8_t*>(pages), rows, Rk, Rv, clip_k, clip_v, fmt, ab, q,
+                       B * Hq, Hq, qscale, qt);
   };
-  const bool def = is_default(fmt);
-  if (rw == 1) {
-    if (def) go(prologue_kernel<1, Rows, true>);
-    else go(prologue_kernel<1, Rows, false>);
-  } else {
-    if (def) go(prologue_kernel<4, Rows, true>);
-    else go(prologue_kernel<4, Rows, false>);
-  }
+  if (is_default(fmt)) go(prologue_kernel<Rows, true>);
+  else go(prologue_kernel<Rows, false>);
   return hipGetLastError();
 }
 }  // namespace
@@ -1200,9 +1165,8 @@ hipError_t launch_prologue(void* pages, int64_t Hkv, const Rows& rows, int64_t n
 hipError_t launch_append(void* pages, int64_t Hkv, const uint16_t* k, const uint16_t* v,
                          const int64_t* slots, int n_tok, const float* Rk, const float* Rv,
                          float clip_k, float clip_v, QuantFmt fmt, hipStream_t st) {
-  const int64_t n_rows = (int64_t)n_tok * Hkv;
-  const PlainRows rows{k, v, slots, (int)n_rows, (int)Hkv};
-  return launch_rows(pages, Hkv, rows, n_rows, Rk, Rv, clip_k, clip_v, fmt, st);
+  const PlainRows rows{k, v, slots, n_tok, (int)Hkv};
+  return launch_rows(pages, rows, Rk, Rv, clip_k, clip_v, fmt, st);
 }
 
 hipError_t launch_mixed_append(void* pages, uint16_t* seg, int64_t Hkv, int S0, int W,
@@ -1211,17 +1175,16 @@ hipError_t launch_mixed_append(void* pages, uint16_t* seg, int64_t Hkv, int S0, 
                                const int32_t* block_table, int max_pages, const float* Rk,
                                const float* Rv, float clip_k, float clip_v, QuantFmt fmt,
                                hipStream_t st) {
-  const int64_t n_rows = (int64_t)n_tok * Hkv;
-  const PrefillRows rows{k, v, seg, seq_idx, pos, seq_lens, block_table, (int)n_rows, (int)Hkv,
+  const PrefillRows rows{k, v, seg, seq_idx, pos, seq_lens, block_table, n_tok, (int)Hkv,
                          max_pages, S0, W};
-  return launch_rows(pages, Hkv, rows, n_rows, Rk, Rv, clip_k, clip_v, fmt, st);
+  return launch_rows(pages, rows, Rk, Rv, clip_k, clip_v, fmt, st);
 }
 
 hipError_t launch_decode_prepare(const uint16_t* q, int B, int Hq, const float* Rk,
                                  float qscale, float* qt, hipStream_t st, int rph, int Hkv) {
   const int rows = B * Hq;
-  hipLaunchKernelGGL(prepare_kernel, dim3(query_blocks(B, Hq, Hkv, rph, kPrepRows)), dim3(256), 0,
-                     st, q, rows, Rk, qscale, qt, rph, Hq, Hkv);
+  hipLaunchKernelGGL(prepare_kernel, dim3(query_blocks(B, Hq, Hkv, rph, kPrepRows)),
+                     dim3(kRotWaves * 64), 0, st, q, rows, Rk, qscale, qt, rph, Hq, Hkv);
   return hipGetLastError();
 }
 
@@ -1230,10 +1193,8 @@ hipError_t launch_step_prologue(void* pages, int64_t Hkv, const uint16_t* k, con
                                 const float* Rv, float clip_k, float clip_v, QuantFmt fmt,
                                 const uint16_t* q, int B, int Hq, float qscale, float* qt,
                                 hipStream_t st) {
-  const int64_t n_rows = (int64_t)n_tok * Hkv;
-  const PlainRows rows{k, v, slots, (int)n_rows, (int)Hkv};
-  return launch_prologue(pages, Hkv, rows, n_rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale,
-                         qt, st);
+  const PlainRows rows{k, v, slots, n_tok, (int)Hkv};
+  return launch_prologue(pages, rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale, qt, st);
 }
 
 hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, int S0, int W,
@@ -1242,10 +1203,8 @@ hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, i
                                       int max_pages, const float* Rk, const float* Rv,
                                       float clip_k, float clip_v, QuantFmt fmt, const uint16_t* q,
                                       int B, int Hq, float qscale, float* qt, hipStream_t st) {
-  const int64_t n_rows = (int64_t)B * Hkv;
-  const StepRows rows{k, v, seg, seq_lens, block_table, (int)n_rows, (int)Hkv, max_pages, S0, W};
-  return launch_prologue(pages, Hkv, rows, n_rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale,
-                         qt, st);
+  const StepRows rows{k, v, seg, seq_lens, block_table, B, (int)Hkv, max_pages, S0, W};
+  return launch_prologue(pages, rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale, qt, st);
 }
 
 hipError_t launch_clip_errors(const uint16_t* x, int64_t n_rows, const float* R,
