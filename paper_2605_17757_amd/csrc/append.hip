@@ -17,7 +17,6 @@
 namespace oscar {
 namespace {
 
-constexpr int kWaves = 4;                // clip calibration: waves per block
 constexpr int kMaxClipCands = 32;  // candidate clip ratios per calibration call
 
 __device__ inline float f16_bits_to_f32(uint16_t h) { return __half2float(__ushort_as_half(h)); }
@@ -31,22 +30,6 @@ __device__ inline uint16_t f16_sat_bits(float f) {
 // A zero point of zero is stored as +0.  This is done on the binary16 bits: the
 // compiler may drop an "x + 0.0f" whose result only feeds fmaxf/fminf.
 __device__ inline uint16_t plus_zero(uint16_t h) { return (h & 0x7fffu) ? h : (uint16_t)0; }
-
-// max / min over the 32 lanes of a half wave: quad swaps and row rotations by 4
-// and 8 (DPP) reduce each row of 16 lanes, the row-pair swap joins rows 2k, 2k+1.
-template <bool MAX>
-__device__ inline float half_wave_reduce(float x) {
-  auto op = [](float a, float b) { return MAX ? fmaxf(a, b) : fminf(a, b); };
-  x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, false)));
-  x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x4E, 0xF, 0xF, false)));
-  x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xF, 0xF, false)));
-  x = op(x, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xF, 0xF, false)));
-  const uint32_t u = __float_as_uint(x);
-  const auto sw = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return op(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-}
-__device__ inline float half_wave_max(float x) { return half_wave_reduce<true>(x); }
-__device__ inline float half_wave_min(float x) { return half_wave_reduce<false>(x); }
 
 // bfloat16 with saturation to +-(largest finite) (round to nearest even on the
 // binary32 bits; finite inputs).
@@ -64,11 +47,6 @@ __device__ inline uint16_t meta_store(const QFmt& q, float f) {
 __device__ inline float meta_load(const QFmt& q, uint16_t h) {
   return q.bf16 ? __uint_as_float((uint32_t)h << 16) : f16_bits_to_f32(h);
 }
-
-struct QOut {
-  uint32_t code;
-  uint16_t s16, z16;
-};
 
 // Scale and zero point of a group with (clipped) minimum a and maximum b, as
 // stored (s16, z16) and as used for the codes (sf, zf); a group whose stored
@@ -99,16 +77,6 @@ __device__ inline uint32_t quant_code(float y, const QParams& p) {
   if (p.deg) return 0u;
   const float r = rintf(__fadd_rn(__fdiv_rn(y, p.sf), p.zf));
   return (uint32_t)fminf(fmaxf(r, 0.0f), 3.0f);
-}
-
-// Quantize one clipped channel value y of a group with minimum a and maximum b.
-__device__ inline QOut quantize(float y, float a, float b, const QFmt& fmt) {
-  const QParams p = quant_params(a, b, fmt);
-  QOut o;
-  o.s16 = p.s16;
-  o.z16 = p.z16;
-  o.code = quant_code(y, p);
-  return o;
 }
 
 // Token-wise clip threshold (App. "Scale Determination and Per-token Clipping
@@ -328,37 +296,6 @@ struct StepRows {
   }
 };
 
-// Group reductions of the one-row-per-wave layout (lane l: channels l, l + 64):
-// with 32-channel groups each value's group is a wave half, with 64 its whole
-// wave, with 128 both values over the wave.
-__device__ inline float wave_max(float x) {
-  x = half_wave_max(x);
-  const uint32_t u = __float_as_uint(x);
-  const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-}
-__device__ inline float wave_min(float x) {
-  x = half_wave_min(x);
-  const uint32_t u = __float_as_uint(x);
-  const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fminf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
-}
-template <bool MAX>
-__device__ inline void group_reduce2(float v0, float v1, int ng, float& r0, float& r1) {
-  auto op = [](float a, float b) { return MAX ? fmaxf(a, b) : fminf(a, b); };
-  auto half = [](float x) { return MAX ? half_wave_max(x) : half_wave_min(x); };
-  auto wave = [](float x) { return MAX ? wave_max(x) : wave_min(x); };
-  if (ng == 4) {
-    r0 = half(v0);
-    r1 = half(v1);
-  } else if (ng == 2) {
-    r0 = wave(v0);
-    r1 = wave(v1);
-  } else {
-    r0 = r1 = wave(op(v0, v1));
-  }
-}
-
 // DEF: the default format (binary16 metadata, group-absmax clip, 32-channel
 // groups) as compile-time constants, so that its code has no format branches.
 __device__ inline QFmt pick(bool def, const QFmt& fmt) { return def ? QFmt{0, 0, 4, 0} : fmt; }
@@ -376,10 +313,9 @@ __device__ inline QFmt pick(bool def, const QFmt& fmt) { return def ? QFmt{0, 0,
 // i holds row l / 16 + 4i, column l % 16; the rows go to LDS in fp32 for the
 // quantizer.
 //
-// Bound: the fp64 matrix core, 4096 cycles per CU and item.  fp64 conversions share
-// its unit, so nothing is converted inside the loop (one wave per item with R as
-// fp32 in LDS converted 9 values per 8 products and kept the matrix core 63 % busy:
-// 131072 tokens x 8 heads 1392 us).
+// For a decode step's few rows, where latency counts: all columns at once on 8 waves
+// (32 products deep), R straight from L2 into registers, nothing converted between
+// the products.  Larger updates use the bulk kernel below.
 // ---------------------------------------------------------------------------
 constexpr int kItemRows = 16;
 // A operand in LDS: channel 4s + k of a row at double 48 k + s of its 177 (reads of
@@ -798,6 +734,38 @@ __device__ inline uint64_t readlane64(uint64_t v, int lane) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// R to LDS by a block of WAVES waves (loads issued before the stores).
+template <int WAVES>
+__device__ inline void stage_rot(float4 (&Rs)[kD][kD / 4], const float* __restrict__ R, int t) {
+  constexpr int kN = kD * kD / 4 / (WAVES * 64);
+  float4 r4[kN];
+#pragma unroll
+  for (int i = 0; i < kN; ++i) r4[i] = reinterpret_cast<const float4*>(R)[t + WAVES * 64 * i];
+#pragma unroll
+  for (int i = 0; i < kN; ++i) (&Rs[0][0])[t + WAVES * 64 * i] = r4[i];
+}
+// One wave's product of the 16 bf16 rows staged in its area and R: column j of tile t
+// is channel 64 (t / 4) + 4 j + t % 4.
+__device__ inline void rotate_wave(const float4 (&Rs)[kD][kD / 4], const uint32_t* area, int l,
+                                   d4v (&acc)[8]) {
+  const int kq = l >> 4, j = l & 15;
+  // v_perm selector: the bf16 of channel 4 s + kq (of the 8 bytes read) into the
+  // high half of a dword, zeros below: an fp32 with the same value
+  const uint32_t asel = 0x01000C0Cu + 0x02020000u * (uint32_t)kq;
+#pragma unroll
+  for (int tt = 0; tt < 8; ++tt) acc[tt] = d4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+  for (int s = 0; s < kD / 4; ++s) {
+    const uint2 xa = *reinterpret_cast<const uint2*>(&area[j * kStagePitch + 2 * s]);
+    const double a = (double)__uint_as_float(__builtin_amdgcn_perm(xa.y, xa.x, asel));
+    const float4 r0 = Rs[4 * s + kq][j], r1 = Rs[4 * s + kq][16 + j];
+    const float rb[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+#pragma unroll
+    for (int tt = 0; tt < 8; ++tt)
+      acc[tt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)rb[tt], acc[tt], 0, 0, 0);
+  }
+}
+
 template <class Rows, bool DEF>
 __global__ __launch_bounds__(kBulkWaves * 64) void append_bulk_kernel(
     uint8_t* __restrict__ pages, Rows rows, const float* __restrict__ Rk,
@@ -810,23 +778,11 @@ __global__ __launch_bounds__(kBulkWaves * 64) void append_bulk_kernel(
   const float* __restrict__ R = is_v ? Rv : Rk;  // nullptr: identity
   const float clip = is_v ? clip_v : clip_k;
   const int t = threadIdx.x, w = t >> 6, l = t & 63, kq = l >> 4, j = l & 15;
-  if (R) {
-    if (fmt.rph) R += (size_t)(bx % Hkv) * kD * kD;  // gx is a multiple of Hkv
-    float4 r4[kD * kD / 4 / (kBulkWaves * 64)];
-#pragma unroll
-    for (int i = 0; i < kD * kD / 4 / (kBulkWaves * 64); ++i)
-      r4[i] = reinterpret_cast<const float4*>(R)[t + kBulkWaves * 64 * i];
-#pragma unroll
-    for (int i = 0; i < kD * kD / 4 / (kBulkWaves * 64); ++i)
-      (&Rs[0][0])[t + kBulkWaves * 64 * i] = r4[i];
-  }
+  if (R) stage_rot<kBulkWaves>(Rs, R + (fmt.rph ? (size_t)(bx % Hkv) * kD * kD : 0), t);  // gx: a multiple of Hkv
   if (t == 0) taken = 0;
   __syncthreads();
   uint32_t* area = area_all[w];
   float* xt = reinterpret_cast<float*>(area);
-  // v_perm selector: the bf16 of channel 4 s + kq (of the 8 bytes read) into the
-  // high half of a dword, zeros below: an fp32 with the same value
-  const uint32_t asel = 0x01000C0Cu + 0x02020000u * (uint32_t)kq;
   const int groups = (rows.n_tok + kItemRows - 1) / kItemRows;
   const int n_items = groups * Hkv, n_mine = (n_items - bx + gx - 1) / gx;
   for (;;) {
@@ -860,18 +816,7 @@ __global__ __launch_bounds__(kBulkWaves * 64) void append_bulk_kernel(
     float x[32];
     if (R) {
       d4v acc[8];
-#pragma unroll
-      for (int tt = 0; tt < 8; ++tt) acc[tt] = d4v{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 1
-      for (int s = 0; s < kD / 4; ++s) {
-        const uint2 xa = *reinterpret_cast<const uint2*>(&area[j * kStagePitch + 2 * s]);
-        const double a = (double)__uint_as_float(__builtin_amdgcn_perm(xa.y, xa.x, asel));
-        const float4 r0 = Rs[4 * s + kq][j], r1 = Rs[4 * s + kq][16 + j];
-        const float rb[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-#pragma unroll
-        for (int tt = 0; tt < 8; ++tt)
-          acc[tt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, (double)rb[tt], acc[tt], 0, 0, 0);
-      }
+      rotate_wave(Rs, area, l, acc);
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf) {
         lane_exchange();  // earlier reads of the area come first
@@ -939,141 +884,219 @@ __global__ __launch_bounds__(kRotWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // ---------------------------------------------------------------------------
 // Clip calibration (Alg. 1 CalibrateClip).  The paper leaves the procedure open;
 // it is read here as: the candidate ratio whose quantization of the rotated
-// calibration rows has the smallest squared error.  A wave takes rows (token,
-// head) grid-stride and rotates each exactly as the cache update does (lane l:
-// channels l and l + 64); for every candidate it clips and quantizes the row with
-// the cache update's steps and adds (x~_c - s (code_c - z))^2 in fp64, s and z
-// read back from their stored format, to the lane's sum for that candidate.  The
-// clip threshold is formed as in the cache update: ratio x group absmax (the
-// group maxima found once per row), or the token quantile a_k + f (a_{k+1} - a_k)
-// read from the row's |x~| sorted once per row (bitonic network over the wave).
-// At the end the lanes, the waves and then (clip_reduce_kernel) the blocks are
-// summed in a fixed order.
+// calibration rows has the smallest squared error.  Independent waves take items
+// (16 tokens of a head; a fixed share, so that sums have a fixed order) and rotate
+// them as the bulk cache update does, in its quad-lane layout (lane: 32 channels of a row); for every
+// candidate a lane clips and quantizes its channels with the cache update's steps
+// and adds (x~_c - s (code_c - z))^2 in fp64, s and z read back from their stored
+// format.  What does not depend on the candidate is done once per item: the groups'
+// extremes (clipping is monotone), and for the token quantile the row's |x~| sorted
+// (a bitonic network over the quad, kept in LDS), of which a candidate reads a_k and
+// a_{k+1}.  Sums are added in a fixed order: over the lanes per item and candidate
+// (lane n keeps candidate n), then the waves, then (clip_reduce_kernel) the blocks.
+//
+// Bound: VALU issue, about 11 instructions per channel and candidate (four of them
+// fp64).  One wave per row, with cross-lane reductions, three divisions per value and
+// the group's parameters formed by every lane for every candidate, took 1112 us per
+// tensor (8878 tokens x 8 heads, 21 candidates, groups of 128 with the quantile).
 // ---------------------------------------------------------------------------
+constexpr int kClipWaves = 8;
+constexpr int kRowPitch = kD + 4;  // floats per x~ row in LDS
+
+// Sum over the wave, the same in every lane: DPP inside rows of 16 lanes, then the
+// row swaps across 16 and 32 lanes.
 __device__ inline double wave_sum_f64(double x) {
+  auto dpp = [](double v, auto ctrl) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, decltype(ctrl)::value, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), decltype(ctrl)::value, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+  };
+  x += dpp(x, std::integral_constant<int, 0xB1>{});
+  x += dpp(x, std::integral_constant<int, 0x4E>{});
+  x += dpp(x, std::integral_constant<int, 0x124>{});
+  x += dpp(x, std::integral_constant<int, 0x128>{});
+  double tot = 0.0;
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
+  for (int k = 0; k < 4; ++k)
+    tot += __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(x), 16 * k));
+  return tot;
 }
 
-// Ascending sort of the 128 values (element 2 l + s in slot s of lane l).
-__device__ inline void wave_sort128(float& v0, float& v1, int l) {
+// Ascending sort of a row's 128 values in the quad-lane layout (element 32 q + i in
+// v[i] of lane q): each lane's 32 by a bitonic network, then two merges over lanes.
+__device__ inline void quad_sort128(float (&v)[32], int q) {
+  auto order = [&](int a, int b) {  // v[a] <= v[b]
+    const float lo = fminf(v[a], v[b]), hi = fmaxf(v[a], v[b]);
+    v[a] = lo;
+    v[b] = hi;
+  };
+  // compare with the elements `mirror`ed or in place of lane q ^ x
+  auto across = [&](auto ctrl, bool mirror, bool low) {
+    float o[32];
 #pragma unroll
-  for (int k = 2; k <= kD; k <<= 1) {
+    for (int i = 0; i < 32; ++i)
+      o[i] = __int_as_float(__builtin_amdgcn_update_dpp(
+          0, __float_as_int(v[mirror ? 31 - i : i]), decltype(ctrl)::value, 0xF, 0xF, false));
 #pragma unroll
-    for (int j = k >> 1; j >= 2; j >>= 1) {
-      const bool lower = ((2 * l) & j) == 0, asc = ((2 * l) & k) == 0;
-      const float o0 = __shfl_xor(v0, j >> 1, 64), o1 = __shfl_xor(v1, j >> 1, 64);
-      v0 = (lower == asc) ? fminf(v0, o0) : fmaxf(v0, o0);
-      v1 = (lower == asc) ? fminf(v1, o1) : fmaxf(v1, o1);
-    }
-    const bool asc = ((2 * l) & k) == 0;  // j = 1: the lane's own pair
-    const float lo = fminf(v0, v1), hi = fmaxf(v0, v1);
-    v0 = asc ? lo : hi;
-    v1 = asc ? hi : lo;
+    for (int i = 0; i < 32; ++i) v[i] = low ? fminf(v[i], o[i]) : fmaxf(v[i], o[i]);
+  };
+  auto merge32 = [&]() {
+#pragma unroll
+    for (int d = 16; d >= 1; d >>= 1)
+#pragma unroll
+      for (int i = 0; i < 32; ++i)
+        if (!(i & d)) order(i, i + d);
+  };
+#pragma unroll
+  for (int k = 2; k <= 32; k <<= 1) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i)  // first step of a merge against the mirrored half
+      if ((i & (k - 1)) < k / 2) order(i, (i & ~(k - 1)) + (k - 1 - (i & (k - 1))));
+#pragma unroll
+    for (int d = k >> 2; d >= 1; d >>= 1)
+#pragma unroll
+      for (int i = 0; i < 32; ++i)
+        if (!(i & d)) order(i, i + d);
   }
-}
-__device__ inline float sorted_at(float v0, float v1, int e) {  // e wave-uniform
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int((e & 1) ? v1 : v0), e >> 1));
+  across(std::integral_constant<int, 0xB1>{}, true, (q & 1) == 0);  // 64: lane ^ 1, mirrored
+  merge32();
+  across(std::integral_constant<int, 0x1B>{}, true, q < 2);         // 128: lane 3 - q, mirrored
+  across(std::integral_constant<int, 0xB1>{}, false, (q & 1) == 0); // distance 32
+  merge32();
 }
 
-__global__ __launch_bounds__(256) void clip_err_kernel(const uint16_t* __restrict__ x, int n_rows,
-                                                       const float* __restrict__ R,
-                                                       const float* __restrict__ cands,
-                                                       int n_cands, QFmt fmt, int Hkv,
-                                                       double* __restrict__ partial) {
-  __shared__ float Rs[kD * kD];
-  __shared__ double xs[kWaves][kD];
-  __shared__ double werr[kWaves][kMaxClipCands];
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  // rph: the block takes the rows (token, h) of one KV head h and its matrix
-  int h = 0, bx = blockIdx.x, gx = gridDim.x;
-  if (fmt.rph) {
-    h = bx % Hkv;
-    bx /= Hkv;
-    gx /= Hkv;
-    if (R) R += (size_t)h * kD * kD;
-  }
-  const int n_seq = fmt.rph ? n_rows / Hkv : n_rows;
-  if (R) {
-    float4 r4[kD * kD / 4 / 256];
-#pragma unroll
-    for (int i = 0; i < kD * kD / 4 / 256; ++i)
-      r4[i] = reinterpret_cast<const float4*>(R)[threadIdx.x + 256 * i];
-#pragma unroll
-    for (int i = 0; i < kD * kD / 4 / 256; ++i) reinterpret_cast<float4*>(Rs)[threadIdx.x + 256 * i] = r4[i];
-  }
+// Up to two tensors (K and V of a layer) in one launch: blockIdx.y.
+struct ClipJobs {
+  const uint16_t* x[2];
+  const float* R[2];
+  double* partial[2];
+  double* err[2];
+  float* best[2];
+};
+
+__global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
+    ClipJobs jobs, int n_tok, const float* __restrict__ cands, int n_cands, QFmt fmt, int Hkv) {
+  __shared__ float4 Rs[kD][kD / 4];                                   // 64 KB
+  __shared__ uint32_t area_all[kClipWaves][kItemRows * kRowPitch];    // 66 KB
+  __shared__ double werr[kClipWaves][kMaxClipCands];
+  const uint16_t* __restrict__ x_all = jobs.x[blockIdx.y];
+  const float* __restrict__ R = jobs.R[blockIdx.y];
+  const int bx = blockIdx.x, gx = gridDim.x;
+  const int t = threadIdx.x, w = t >> 6, l = t & 63, kq = l >> 4, j = l & 15;
+  if (R) stage_rot<kClipWaves>(Rs, R + (fmt.rph ? (size_t)(bx % Hkv) * kD * kD : 0), t);  // gx: a multiple of Hkv
   __syncthreads();
-  double e[kMaxClipCands];
+  uint32_t* area = area_all[w];
+  float* xt = reinterpret_cast<float*>(area);
+  const int n_items = (n_tok + kItemRows - 1) / kItemRows * Hkv, n_mine = (n_items - bx + gx - 1) / gx;
+  const int rr = l >> 2, q = l & 3;
+  double mine = 0.0;  // lane n: the wave's error of candidate n
+  auto clamp = [](float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); };
+  for (int n = w; n < n_mine; n += kClipWaves) {
+    const int item = bx + n * gx, tok0 = item / Hkv * kItemRows, h = item % Hkv;
+    const uint16_t* src = x_all + ((size_t)tok0 * Hkv + h) * kD;
+    uint32_t row[kItemRows];
 #pragma unroll
-  for (int n = 0; n < kMaxClipCands; ++n) e[n] = 0.0;
-  for (int i = bx * kWaves + w; i < n_seq; i += gx * kWaves) {
-    const int row = fmt.rph ? i * Hkv + h : i;
-    const uint32_t pair = reinterpret_cast<const uint32_t*>(x + (size_t)row * kD)[l];
-    lane_exchange();  // the previous row's reads of xs[w] come first
-    xs[w][2 * l] = (double)__uint_as_float(pair << 16);
-    xs[w][2 * l + 1] = (double)__uint_as_float(pair & 0xffff0000u);
+    for (int r = 0; r < kItemRows; ++r)
+      row[r] = tok0 + r < n_tok ? reinterpret_cast<const uint32_t*>(src + (size_t)r * Hkv * kD)[l] : 0u;
+    lane_exchange();  // the previous item's reads of the wave's area come first
+#pragma unroll
+    for (int r = 0; r < kItemRows; ++r) area[r * kStagePitch + l] = row[r];
     lane_exchange();
-    double acc0 = 0.0, acc1 = 0.0;
+    float x[32];
     if (R) {
-#pragma unroll 4
-      for (int c = 0; c < kD; ++c) {
-        const double xc = xs[w][c];
-        acc0 = __fma_rn(xc, (double)Rs[c * kD + l], acc0);
-        acc1 = __fma_rn(xc, (double)Rs[c * kD + l + 64], acc1);
+      d4v acc[8];
+      rotate_wave(Rs, area, l, acc);
+      lane_exchange();
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+          *reinterpret_cast<float4*>(xt + (kq + 4 * i) * kRowPitch + 64 * hf + 4 * j) =
+              make_float4(__double2float_rn(acc[4 * hf][i]), __double2float_rn(acc[4 * hf + 1][i]),
+                          __double2float_rn(acc[4 * hf + 2][i]), __double2float_rn(acc[4 * hf + 3][i]));
+      lane_exchange();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float4 v = *reinterpret_cast<const float4*>(xt + rr * kRowPitch + 32 * q + 4 * i);
+        x[4 * i] = v.x; x[4 * i + 1] = v.y; x[4 * i + 2] = v.z; x[4 * i + 3] = v.w;
       }
     } else {
-      acc0 = xs[w][l];
-      acc1 = xs[w][l + 64];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t pr = area[rr * kStagePitch + 16 * q + i];
+        x[2 * i] = __uint_as_float(pr << 16);
+        x[2 * i + 1] = __uint_as_float(pr & 0xffff0000u);
+      }
     }
-    const float xt0 = __double2float_rn(acc0), xt1 = __double2float_rn(acc1);
-    float g0, g1, s0 = 0.0f, s1 = 0.0f;
+    float mn = x[0], mx = x[0];
+#pragma unroll
+    for (int i = 1; i < 32; ++i) {
+      mn = fminf(mn, x[i]);
+      mx = fmaxf(mx, x[i]);
+    }
+    mn = quad_group_min(mn, fmt.ng);
+    mx = quad_group_max(mx, fmt.ng);
     if (fmt.quantile) {
-      s0 = fabsf(xt0);
-      s1 = fabsf(xt1);
-      wave_sort128(s0, s1, l);
-    } else {
-      group_reduce2<true>(fabsf(xt0), fabsf(xt1), fmt.ng, g0, g1);
+      float v[32];
+#pragma unroll
+      for (int i = 0; i < 32; ++i) v[i] = fabsf(x[i]);
+      quad_sort128(v, q);
+      lane_exchange();  // every lane's reads of the area come first
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        *reinterpret_cast<float4*>(xt + rr * kRowPitch + 32 * q + 4 * i) =
+            make_float4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+      lane_exchange();
     }
-#pragma clang loop unroll(full)
-    for (int n = 0; n < kMaxClipCands; ++n) {
-      if (n >= n_cands) continue;
-      const float clip = cands[n];
-      float tau0, tau1;
+    const bool live = tok0 + rr < n_tok;
+    double x64[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) x64[i] = (double)x[i];
+#pragma unroll 1
+    for (int n_c = 0; n_c < n_cands; ++n_c) {
+      const float clip = cands[n_c];
+      float tau;
       if (fmt.quantile) {
         int k;
         float f;
         quantile_pos(clip, k, f);
-        k = __builtin_amdgcn_readfirstlane(k);
-        const float ak = sorted_at(s0, s1, k);
-        tau0 = tau1 = k >= kD - 1 ? ak : lerp_tau(ak, sorted_at(s0, s1, k + 1), f);
+        const float ak = xt[rr * kRowPitch + k], ak1 = xt[rr * kRowPitch + min(k + 1, kD - 1)];
+        tau = k >= kD - 1 ? ak : lerp_tau(ak, ak1, f);
       } else {
-        tau0 = __fmul_rn(clip, g0);
-        tau1 = __fmul_rn(clip, g1);
+        tau = __fmul_rn(clip, fmaxf(fmaxf(-mn, mx), 0.0f));
       }
-      const float y0 = fminf(fmaxf(xt0, -tau0), tau0), y1 = fminf(fmaxf(xt1, -tau1), tau1);
-      float a0, a1, b0, b1;
-      group_reduce2<false>(y0, y1, fmt.ng, a0, a1);
-      group_reduce2<true>(y0, y1, fmt.ng, b0, b1);
-      const QOut q0 = quantize(y0, a0, b0, fmt);
-      const QOut q1 = quantize(y1, a1, b1, fmt);
-      const double d0 = (double)xt0 - (double)meta_load(fmt, q0.s16) *
-                                          ((double)q0.code - (double)meta_load(fmt, q0.z16));
-      const double d1 = (double)xt1 - (double)meta_load(fmt, q1.s16) *
-                                          ((double)q1.code - (double)meta_load(fmt, q1.z16));
-      e[n] += d0 * d0 + d1 * d1;
+      const QParams p = quant_params(clamp(mn, -tau, tau), clamp(mx, -tau, tau), fmt);
+      const double s64 = (double)meta_load(fmt, p.s16), z64 = (double)meta_load(fmt, p.z16);
+      double e0 = 0.0, e1 = 0.0;
+      if (fmt.bf16 && __any(!p.deg && !fast_scale(p.sf))) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+          const double d = __fma_rn(-s64, (double)quant_code(clamp(x[i], -tau, tau), p) - z64, x64[i]);
+          e0 = __fma_rn(d, d, e0);
+        }
+      } else {
+        const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+          const float d = div_by_scale(clamp(x[i], -tau, tau), s, r);
+          const float code = rintf(clamp(__fadd_rn(d, p.zf), 0.0f, 3.0f));
+          const double u = __fma_rn(-s64, (double)code - z64, x64[i]);
+          if (i & 1) e1 = __fma_rn(u, u, e1);
+          else e0 = __fma_rn(u, u, e0);
+        }
+      }
+      const double tot = wave_sum_f64(live ? e0 + e1 : 0.0);
+      if (l == n_c) mine += tot;
     }
   }
-#pragma unroll
-  for (int n = 0; n < kMaxClipCands; ++n) {
-    if (n >= n_cands) continue;
-    const double t = wave_sum_f64(e[n]);
-    if (l == 0) werr[w][n] = t;
-  }
+  if (l < kMaxClipCands) werr[w][l] = mine;
   __syncthreads();
-  if ((int)threadIdx.x < n_cands) {
-    const int n = threadIdx.x;
-    partial[(size_t)blockIdx.x * n_cands + n] = ((werr[0][n] + werr[1][n]) + werr[2][n]) + werr[3][n];
+  if (t < n_cands) {
+    double tot = 0.0;
+#pragma unroll
+    for (int k = 0; k < kClipWaves; ++k) tot += werr[k][t];
+    jobs.partial[blockIdx.y][(size_t)bx * n_cands + t] = tot;
   }
 }
 
@@ -1083,9 +1106,10 @@ __global__ __launch_bounds__(256) void clip_err_kernel(const uint16_t* __restric
 constexpr int kClipParts = 8;
 
 __global__ __launch_bounds__(kClipParts * kMaxClipCands) void clip_reduce_kernel(
-    const double* __restrict__ partial, int n_blocks, int n_cands,
-    const float* __restrict__ cands, double inv_n, double* __restrict__ err,
-    float* __restrict__ best) {
+    ClipJobs jobs, int n_blocks, int n_cands, const float* __restrict__ cands, double inv_n) {
+  const double* __restrict__ partial = jobs.partial[blockIdx.x];
+  double* __restrict__ err = jobs.err[blockIdx.x];
+  float* __restrict__ best = jobs.best[blockIdx.x];
   __shared__ double ps[kClipParts][kMaxClipCands];
   __shared__ double es[kMaxClipCands];
   const int n = threadIdx.x % kMaxClipCands, part = threadIdx.x / kMaxClipCands;
@@ -1207,23 +1231,34 @@ hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, i
   return launch_prologue(pages, rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale, qt, st);
 }
 
-hipError_t launch_clip_errors(const uint16_t* x, int64_t n_rows, const float* R,
+hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t n_tok,
                               const float* cands, int n_cands, QuantFmt fmt, int Hkv,
-                              double* partial, int n_blocks, double* err, float* best,
                               hipStream_t st) {
-  hipLaunchKernelGGL(clip_err_kernel, dim3((unsigned)n_blocks), dim3(256), 0, st, x, (int)n_rows, R,
-                     cands, n_cands, fmt, Hkv, partial);
+  ClipJobs jobs{};
+  for (int i = 0; i < n_tensors; ++i) {
+    jobs.x[i] = tensors[i].x;
+    jobs.R[i] = tensors[i].R;
+    jobs.partial[i] = tensors[i].partial;
+    jobs.err[i] = tensors[i].err;
+    jobs.best[i] = tensors[i].best;
+  }
+  // one block per CU over all tensors, and no more than the workspace has room for
+  const int nb = std::min(append_blocks(append_items((int)n_tok, Hkv), Hkv, fmt.rph,
+                                        device_cus() / n_tensors),
+                          clip_blocks(n_tok * Hkv, Hkv, fmt.rph));
+  hipLaunchKernelGGL(clip_err_kernel, dim3((unsigned)nb, (unsigned)n_tensors), dim3(kClipWaves * 64),
+                     0, st, jobs, (int)n_tok, cands, n_cands, fmt, Hkv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(clip_reduce_kernel, dim3(1), dim3(kClipParts * kMaxClipCands), 0, st, partial,
-                     n_blocks, n_cands,
-                     cands, 1.0 / ((double)n_rows * kD), err, best);
+  hipLaunchKernelGGL(clip_reduce_kernel, dim3((unsigned)n_tensors), dim3(kClipParts * kMaxClipCands),
+                     0, st, jobs, nb, n_cands, cands, 1.0 / ((double)(n_tok * Hkv) * kD));
   return hipGetLastError();
 }
 
+// Blocks that a tensor's partial errors have room for in the workspace.
 int clip_blocks(int64_t n_rows, int Hkv, int rph) {
   const int64_t heads = rph ? Hkv : 1;  // rph: blocks per head, times Hkv
-  const int64_t items = (n_rows / heads + kWaves - 1) / kWaves;
+  const int64_t items = (n_rows / heads + 3) / 4;
   const int64_t cap = std::max<int64_t>(1, 4 * (int64_t)device_cus() / heads);
   return (int)(std::max<int64_t>(1, std::min(items, cap)) * heads);
 }

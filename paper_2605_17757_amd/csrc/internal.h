@@ -194,14 +194,20 @@ hipError_t launch_eig(const double* C, int n_mats, int max_sweeps, double* diag,
                       hipStream_t st);
 // R = U H_Had P_br for n_mats matrices (either output may be nullptr).
 hipError_t launch_compose(const double* U, int n_mats, double* R64, float* R32, hipStream_t st);
-// Mean squared quantization error of the rotated rows for each candidate clip
-// ratio (n_cands <= 32) and the first minimizing candidate; partial: n_blocks x
-// n_cands doubles, n_blocks = clip_blocks(n_rows).
-// Rows x [n_rows / Hkv][Hkv][128]; with fmt.rph, R is [Hkv][128][128].
+// Mean squared quantization error of the rotated rows x [n_tok][Hkv][128] of each
+// tensor (at most two) for each candidate clip ratio (n_cands <= 32) and the first
+// minimizing candidate; with fmt.rph, R is [Hkv][128][128].  partial:
+// clip_blocks(n_tok * Hkv, Hkv, rph) x n_cands doubles of its own per tensor.
+struct ClipTensor {
+  const uint16_t* x;
+  const float* R;
+  double* partial;
+  double* err;
+  float* best;
+};
 int clip_blocks(int64_t n_rows, int Hkv, int rph);
-hipError_t launch_clip_errors(const uint16_t* x, int64_t n_rows, const float* R,
+hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t n_tok,
                               const float* cands, int n_cands, QuantFmt fmt, int Hkv,
-                              double* partial, int n_blocks, double* err, float* best,
                               hipStream_t st);
 
 }  // namespace oscar

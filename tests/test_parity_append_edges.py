@@ -70,3 +70,29 @@ def test_append_edges(fmt, n_tok, Hkv):
         diff = int((pool.cpu().numpy() != want).sum())
         log(fmt, n_tok, Hkv, rho, "differing bytes", diff)
         assert diff == 0
+
+
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("n_tok,Hkv,n_cands", [(1, 1, 1), (17, 3, 32), (47, 2, 9)])
+def test_clip_errors_edges(fmt, n_tok, Hkv, n_cands):
+    """calib_clip at the edges of its 16-token items and of the candidate count, on
+    the same degenerate rows.  Error sums: the same fp64 terms in another order, the
+    term (x~ - s (code - z))^2 with one rounding fewer, so within the few roundings of
+    the cancellation in x~ - s (code - z), at most |x~| 2^-52 each: relative to the
+    rows' mean square, 1e-12 covers them with room."""
+    G, meta, clip_mode, rk, _, rph = FORMATS[fmt]
+    seed = 77 * n_tok + Hkv
+    lay = ok.Layout(Hkv, 1, group_size=G, clip_mode=clip_mode, meta_dtype=meta, rot_per_head=rph)
+    R = np.stack([W.rotation(seed + h) for h in range(Hkv if rph else 1)])
+    R = np.ascontiguousarray(R if rph else R[0]) if rk else None
+    x = _rows(n_tok, Hkv, seed)
+    x = x.float().clamp(-1e3, 1e3).to(torch.bfloat16)  # errors of one size
+    cands = np.linspace(0.31, 1.0, n_cands).astype(np.float32)
+    err, best = ok.calib_clip(lay, x.cuda(), None if R is None else torch.from_numpy(R).cuda(),
+                              torch.from_numpy(cands).cuda())
+    torch.cuda.synchronize()
+    want = oracle.clip_errors(bits(x), R, G=G, cands=cands, meta=meta, clip=clip_mode)
+    got, ms = err.cpu().numpy(), float(x.double().square().mean())
+    log(fmt, n_tok, Hkv, "max error over mean square", float(np.max(np.abs(got - want))) / max(ms, 1e-300))
+    assert np.all(np.abs(got - want) <= 1e-12 * ms)
+    assert float(best.cpu()[0]) == float(cands[int(np.argmin(got))])
