@@ -377,192 +377,334 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_kernel(
 
 // ---------------------------------------------------------------------------
 // Symmetric eigen-decomposition by cyclic Jacobi (round-robin ordering), fp64.
-// One block of 16 waves per matrix keeps the whole matrix in LDS (130 KB, both
-// triangles: plain row-major addressing for the block updates).  A sweep is 127
-// rounds of 64 disjoint pairs (p, q) (circle method: in round r the pairs are
-// (127, r) and ((r + k) mod 127, (r - k) mod 127), k = 1..63), so every
-// off-diagonal entry is visited once per sweep.  For each pair the rotation
-// J (J_pp = J_qq = c, J_pq = s, J_qp = -s) with tau = (a_qq - a_pp) / (2 a_pq),
-// t = sign(tau) / (|tau| + sqrt(1 + tau^2)), c = 1 / sqrt(1 + t^2), s = t c
-// zeroes a_pq (Golub and Van Loan, symmetric Schur decomposition); the round
-// applies A <- J^T A J as independent 2x2 block updates.  A pair is skipped when
-// |a_pq| <= 1e-15 sqrt(|a_pp a_qq|); the sweeps stop when a sweep skips every
-// pair (info = sweeps run, or -1 if max_sweeps did not converge).  The rounds' (c, s) are recorded; jacobi_vectors_kernel multiplies them
-// into the eigenvectors afterwards (the vectors do not fit in LDS next to A).
+// A sweep is 127 rounds of 64 disjoint pairs (circle method: in round r pair 0 is
+// (127, r) and pair k is (a, b) = ((r + k) mod 127, (r - k) mod 127), k = 1..63), so
+// every off-diagonal entry is visited once per sweep.  For each pair, p = min(a, b),
+// q = max(a, b), the rotation J (J_pp = J_qq = c, J_pq = s, J_qp = -s) with
+// tau = (a_qq - a_pp) / (2 a_pq), t = sign(tau) / (|tau| + sqrt(1 + tau^2)),
+// c = 1 / sqrt(1 + t^2), s = t c zeroes a_pq (Golub and Van Loan, symmetric Schur
+// decomposition); the round applies A <- J^T A J as independent 2x2 block updates.
+// A pair is skipped when |a_pq| <= 1e-15 sqrt(|a_pp a_qq|); the sweeps stop when a
+// sweep skips every pair (info = sweeps run, or -1 if max_sweeps did not converge).
+//
+// One block of 16 waves per matrix.  The rounds are a dependent chain (some 1,800 of
+// them), so a round has to be short; the matrix is kept in pair space to that end:
+// block (k1, k2), k1 < k2, holds the entries of pairs k1 and k2 of the current
+// round, and from one round to the next the indices move by one pair,
+//   a'_0 = a_0, a'_k = a_(k+1) (k = 1..62), a'_63 = b_63,
+//   b'_0 = a_1, b'_k = b_(k-1) (k = 1..63),
+// the same in every round.  So a thread's blocks read their four entries from four
+// fixed places of the last round's buffer and write them to one of the other buffer
+// (one barrier per round, each entry read and written once, no index arithmetic).  Lane k of wave 0 holds pair k's diagonal block, takes the block
+// whose entries become the pair's next off-diagonal entry, and forms the next
+// round's rotation while the other waves update.  Its 64 blocks are those whose
+// entry comes from within a pair, which therefore never leaves the lane.
+// Rotations are kept as (c, s~), s~ = s if a < b, -s otherwise: a' = c a - s~ b and
+// b' = s~ a + c b are then the two rows of J^T, in either order.  They are recorded
+// for jacobi_vectors_kernel.  Bound: LDS and fp64 VALU of the updates, 0.86 us of a
+// round alone, the rotations 0.43 us; 1670 us for two matrices of 14 and 10 sweeps
+// (the whole matrix in index order, with the rotations formed between two barriers:
+// 2.0 us a round, 3593 us).
 // ---------------------------------------------------------------------------
 constexpr int kJacRounds = kD - 1;
 constexpr int kJacPairs = kD / 2;
-constexpr int kJacPitch = kD + 2;  // doubles: rows of the LDS copy, 8 bytes of padding
-constexpr int kJacBlocks = kJacPairs * (kJacPairs + 1) / 2;  // 2x2 blocks with k1 <= k2
+constexpr int kJacWaves = 16;
+constexpr int kJacThreads = kJacWaves * 64;
+// A buffer holds the blocks in 32 rows of 64 (padded: fewer bank conflicts), block
+// rows k1 and 62 - k1 (63 - k1 and k1 + 1 blocks) end to end, so that a wave takes a
+// row and most of its accesses are consecutive; element (t1, t2) in plane 2 t1 + t2.
+constexpr int kJacRows = kJacPairs / 2;
+constexpr int kJacPitch = kJacPairs + 1;
+constexpr int kJacPlane = kJacRows * kJacPitch;
+constexpr int kJacPerThread = (kJacRows + kJacWaves - 2) / (kJacWaves - 1);  // of the waves other than wave 0
 constexpr double kJacTol = 1e-15;
 
-__device__ inline void round_pair(int r, int kk, int& p, int& q) {
-  int a, b;
-  if (kk == 0) {
-    a = kD - 1;
-    b = r;
-  } else {
-    a = (r + kk) % kJacRounds;
-    b = (r - kk + kJacRounds) % kJacRounds;
+// Indices of pair k in round 0.
+__device__ inline int jac_a(int k) { return k == 0 ? kD - 1 : k; }
+__device__ inline int jac_b(int k) { return k == 0 ? 0 : kJacRounds - k; }
+// Place of element (t1, t2) (0: a, 1: b) of pairs k1 != k2 in a buffer.
+__device__ inline int jac_place(int k1, int t1, int k2, int t2) {
+  if (k1 > k2) {
+    const int k = k1, t = t1;
+    k1 = k2;
+    t1 = t2;
+    k2 = k;
+    t2 = t;
   }
-  p = min(a, b);
-  q = max(a, b);
+  const int row = min(k1, kJacPairs - 2 - k1), col = k1 < kJacRows ? k2 - k1 - 1 : k2;
+  return (2 * t1 + t2) * kJacPlane + row * kJacPitch + col;
+}
+// Pair and side that index t of pair k had one round before.
+__device__ inline void jac_from(int k, int t, int& kf, int& tf) {
+  if (t == 0) {
+    kf = k == 0 ? 0 : k == kJacPairs - 1 ? k : k + 1;
+    tf = k == kJacPairs - 1 ? 1 : 0;
+  } else {
+    kf = k == 0 ? 1 : k - 1;
+    tf = k == 0 ? 0 : 1;
+  }
+}
+// Block at lane l of a row, if it is one of the waves other than wave 0 (which takes
+// (0, 1), (62, 63) and those with k2 = k1 + 2).
+__device__ inline bool jac_block(int row, int l, int& k1, int& k2) {
+  k1 = l < kJacPairs - 1 - row ? row : kJacPairs - 2 - row;
+  k2 = k1 == row ? row + 1 + l : l;
+  if (row == kJacRows - 1 && l >= kJacRows) return false;  // the middle row is half a row
+  return k2 != k1 + 2 && !(k1 == 0 && k2 == 1) && k1 != kJacPairs - 2;
 }
 
-constexpr int kJacThreads = 1024;  // 16 waves: the round's 2080 block updates, ~2 per thread
-constexpr int kJacPerThread = (kJacBlocks + kJacThreads - 1) / kJacThreads;
+// Rotation of a pair with diagonal entries daa, dbb and off-diagonal entry dab: (c,
+// s~); any: whether it is one (not skipped).
+__device__ inline double2 jac_rotation(double daa, double dbb, double dab, bool a_first, bool& any) {
+  const double app = a_first ? daa : dbb, aqq = a_first ? dbb : daa;
+  double c = 1.0, s = 0.0;
+  any = dab != 0.0 && fabs(dab) > kJacTol * sqrt(fabs(app * aqq));
+  if (any) {
+    const double tau = (aqq - app) / (2.0 * dab);
+    const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+    c = 1.0 / sqrt(1.0 + t * t);
+    s = t * c;
+  }
+  return make_double2(c, a_first ? s : -s);
+}
+
+// Entries (aa, ab, ba, bb) of a block under the rotations of its two pairs.
+__device__ inline void jac_update(double (&m)[4], double2 r1, double2 r2) {
+  const double t00 = r1.x * m[0] - r1.y * m[2], t01 = r1.x * m[1] - r1.y * m[3];
+  const double t10 = r1.y * m[0] + r1.x * m[2], t11 = r1.y * m[1] + r1.x * m[3];
+  m[0] = t00 * r2.x - t01 * r2.y;
+  m[1] = t00 * r2.y + t01 * r2.x;
+  m[2] = t10 * r2.x - t11 * r2.y;
+  m[3] = t10 * r2.y + t11 * r2.x;
+}
+
+// Lane i's value of lane i + 1 (UP) or i - 1; `edge` in the lane that has none.
+template <bool UP>
+__device__ inline double lane_shift(double edge, double v) {
+  constexpr int kCtrl = UP ? 0x130 : 0x138;  // wave_shl:1, wave_shr:1
+  const uint64_t e = (uint64_t)__double_as_longlong(edge), u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)e, (int)(uint32_t)u, kCtrl, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(e >> 32), (int)(uint32_t)(u >> 32), kCtrl, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// One round's move of values held per pair (a, b in lane k).
+__device__ inline void jac_move(double& a, double& b, int l) {
+  const double up = lane_shift<true>(b, a);  // a_(k+1); lane 63: b_63
+  b = lane_shift<false>(up, b);              // b_(k-1); lane 0: a_1
+  a = l == 0 ? a : up;
+}
+
+struct JacSmem {
+  double buf[2][4 * kJacPlane];  // 130 KB
+  double2 cs[2][kJacPairs];      // by round parity
+  int rotated[2];                // by sweep parity
+};
+
+// A thread's block: pairs k1 < k2, its place in a buffer and those of its entries
+// one round before.
+struct JacBlock {
+  int k1, k2, own, from[4];
+};
+// The places of block (k1, k2), and its entries of round 0 into them; returns the
+// entry that comes from within a pair (at most one), or -1, and its value in v.
+__device__ inline int jac_place_block(JacBlock& blk, double* buf, const double* __restrict__ Cm,
+                                      int k1, int k2, double& v) {
+  auto index = [](int k, int t) { return t == 0 ? jac_a(k) : jac_b(k); };
+  int inner = -1;
+  blk.k1 = k1;
+  blk.k2 = k2;
+  blk.own = jac_place(k1, 0, k2, 0);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    int ka, ta, kb, tb;
+    jac_from(k1, e >> 1, ka, ta);
+    jac_from(k2, e & 1, kb, tb);
+    const double x = Cm[index(k1, e >> 1) * kD + index(k2, e & 1)];
+    if (ka == kb) {
+      inner = e;
+      v = x;
+      blk.from[e] = 0;
+    } else {
+      blk.from[e] = jac_place(ka, ta, kb, tb);
+      buf[blk.from[e]] = x;
+    }
+  }
+  return inner;
+}
+
+// Wave 0: the pairs' diagonal blocks (lane l: pair l), the rotations, and the block
+// that holds the pair's next off-diagonal entry.
+__device__ inline void jac_lead(JacSmem& sm, const double* __restrict__ Cm, int max_sweeps,
+                                double2* __restrict__ rm, double* __restrict__ diag,
+                                int* __restrict__ n_rounds, int* __restrict__ info) {
+  __builtin_amdgcn_s_setprio(3);  // the round waits for this wave
+  const int l = threadIdx.x;
+  JacBlock blk;
+  double dab_old = 0.0;
+  const int inner = jac_place_block(blk, sm.buf[0], Cm, l == 0 ? 0 : l - 1,
+                                    l == 0 ? 1 : l == kJacPairs - 1 ? l : l + 1, dab_old);
+  const int ia = jac_a(l), ib = jac_b(l);
+  double daa = Cm[ia * kD + ia], dbb = Cm[ib * kD + ib], dab = Cm[ia * kD + ib];
+  bool any, af = ia < ib;  // any rotation in the sweep so far; a < b in this round
+  double2 mine = jac_rotation(daa, dbb, dab, af, any);
+  sm.cs[0][l] = mine;
+  rm[l] = mine;
+  rm += kJacPairs;
+  __syncthreads();
+  int sweeps = 0, converged = 0, cur = 0;
+  for (int sw = 0; sw < max_sweeps; ++sw) {
+    for (int r = 0; r < kJacRounds; ++r, cur ^= 1) {
+      const double* src = sm.buf[cur];
+      double m[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = src[blk.from[e]];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = e == inner ? dab_old : m[e];
+      // rotations of pairs l - 1 (lane 0: 0) and l + 1 (lane 63: 63), the block's two
+      const double2 r1 = make_double2(lane_shift<false>(mine.x, mine.x), lane_shift<false>(mine.y, mine.y));
+      const double2 r2 = make_double2(lane_shift<true>(mine.x, mine.x), lane_shift<true>(mine.y, mine.y));
+      jac_update(m, r1, r2);
+      if (mine.y != 0.0) {  // the pair's own block; its off-diagonal entry is zero by construction
+        const double app = af ? daa : dbb, aqq = af ? dbb : daa, c = mine.x, s = af ? mine.y : -mine.y;
+        const double t00 = c * app - s * dab, t01 = c * dab - s * aqq;
+        const double t10 = s * app + c * dab, t11 = s * dab + c * aqq;
+        const double npp = t00 * c - t01 * s, nqq = t10 * s + t11 * c;
+        daa = af ? npp : nqq;
+        dbb = af ? nqq : npp;
+        dab = 0.0;
+      }
+      dab_old = dab;
+      dab = l == 0 ? m[0] : l == kJacPairs - 1 ? m[3] : m[2];
+      jac_move(daa, dbb, l);
+      const bool last = r == kJacRounds - 1;
+      if (last) {
+        const bool sweep_any = __any(any);
+        if (l == 0) sm.rotated[sw & 1] = sweep_any;
+        any = false;
+      }
+      const int rn = last ? 0 : r + 1;
+      const int a = rn + l, b = rn - l;
+      af = l != 0 && (a >= kJacRounds ? a - kJacRounds : a) < (b < 0 ? b + kJacRounds : b);
+      bool now;
+      mine = jac_rotation(daa, dbb, dab, af, now);
+      any |= now;
+      sm.cs[cur ^ 1][l] = mine;
+      if (!last || sw + 1 < max_sweeps) rm[l] = mine;
+      rm += kJacPairs;
+      double* dst = sm.buf[cur ^ 1] + blk.own;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dst[e * kJacPlane] = m[e];
+      __syncthreads();
+    }
+    if (!sm.rotated[sw & 1]) {  // a sweep without rotations: converged (its identity rounds are not kept)
+      converged = 1;
+      break;
+    }
+    sweeps = sw + 1;
+  }
+  diag[ia] = daa;  // the pairs are back at round 0
+  diag[ib] = dbb;
+  if (l == 0) {
+    *n_rounds = sweeps * kJacRounds;
+    *info = converged ? sweeps + 1 : -1;
+  }
+}
+
+// The other waves: the other blocks, two or three per thread.
+__device__ inline void jac_follow(JacSmem& sm, const double* __restrict__ Cm, int max_sweeps) {
+  JacBlock blk[kJacPerThread];
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+#pragma unroll
+  for (int n = 0; n < kJacPerThread; ++n) {
+    const int row = w - 1 + (kJacWaves - 1) * n;
+    int k1, k2;
+    double none;
+    blk[n].k1 = -1;
+    if (row < kJacRows && jac_block(row, l, k1, k2))
+      jac_place_block(blk[n], sm.buf[0], Cm, k1, k2, none);
+  }
+  __syncthreads();
+  int cur = 0;
+  for (int sw = 0; sw < max_sweeps; ++sw) {
+    for (int r = 0; r < kJacRounds; ++r, cur ^= 1) {
+      const double* src = sm.buf[cur];
+#pragma unroll
+      for (int n = 0; n < kJacPerThread; ++n) {
+        if (blk[n].k1 < 0) continue;
+        double m[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] = src[blk[n].from[e]];
+        jac_update(m, sm.cs[cur][blk[n].k1], sm.cs[cur][blk[n].k2]);
+        double* dst = sm.buf[cur ^ 1] + blk[n].own;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[e * kJacPlane] = m[e];
+      }
+      __syncthreads();
+    }
+    if (!sm.rotated[sw & 1]) break;
+  }
+}
 
 __global__ __launch_bounds__(kJacThreads) void jacobi_kernel(const double* __restrict__ C, int max_sweeps,
                                                      double* __restrict__ diag,
                                                      double2* __restrict__ rot,
                                                      int* __restrict__ n_rounds,
                                                      int* __restrict__ info) {
-  __shared__ double A[kD * kJacPitch];  // both triangles (130 KB)
-  __shared__ double2 cs[kJacPairs];
-  __shared__ int pp[kJacPairs], qq[kJacPairs];
-  __shared__ int rotated;
-  const int mtx = blockIdx.x, tid = threadIdx.x;
+  __shared__ JacSmem sm;
+  const int mtx = blockIdx.x;
   const double* Cm = C + (size_t)mtx * kD * kD;
-  for (int e = tid; e < kD * kD; e += kJacThreads) {
-    const int i = e >> 7, j = e & (kD - 1);
-    A[i * kJacPitch + j] = Cm[e];
-  }
-  // this thread's 2x2 blocks (k1 <= k2), fixed for every round
-  int bk1[kJacPerThread], bk2[kJacPerThread];
-#pragma unroll
-  for (int n = 0; n < kJacPerThread; ++n) {
-    const int b = tid + kJacThreads * n;
-    int k1 = 0, rem = b;
-    while (k1 < kJacPairs && rem >= kJacPairs - k1) {
-      rem -= kJacPairs - k1;
-      ++k1;
-    }
-    bk1[n] = b < kJacBlocks ? k1 : -1;
-    bk2[n] = k1 + rem;
-  }
-  double2* rm = rot + (size_t)mtx * max_sweeps * kJacRounds * kJacPairs;
-  int sweeps = 0, converged = 0;
-  for (int sw = 0; sw < max_sweeps; ++sw) {
-    __syncthreads();
-    if (tid == 0) rotated = 0;
-    for (int r = 0; r < kJacRounds; ++r) {
-      __syncthreads();
-      if (tid < kJacPairs) {
-        int p, q;
-        round_pair(r, tid, p, q);
-        const double app = A[p * kJacPitch + p], aqq = A[q * kJacPitch + q];
-        const double apq = A[p * kJacPitch + q];
-        double c = 1.0, s = 0.0;
-        if (apq != 0.0 && fabs(apq) > kJacTol * sqrt(fabs(app * aqq))) {
-          const double tau = (aqq - app) / (2.0 * apq);
-          const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + t * t);
-          s = t * c;
-          rotated = 1;
-        }
-        cs[tid] = make_double2(c, s);
-        pp[tid] = p;
-        qq[tid] = q;
-        rm[((size_t)sw * kJacRounds + r) * kJacPairs + tid] = make_double2(c, s);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int n = 0; n < kJacPerThread; ++n) {
-        const int k1 = bk1[n], k2 = bk2[n];
-        if (k1 < 0) continue;
-        const double2 c1 = cs[k1], c2 = cs[k2];
-        if (c1.y == 0.0 && c2.y == 0.0) continue;
-        const int p1 = pp[k1], q1 = qq[k1], p2 = pp[k2], q2 = qq[k2];
-        if (k1 == k2) {
-          const double app = A[p1 * kJacPitch + p1], aqq = A[q1 * kJacPitch + q1];
-          const double apq = A[p1 * kJacPitch + q1];
-          const double c = c1.x, s = c1.y;
-          // J^T M J with M symmetric; the off-diagonal entry is zero by construction
-          const double t00 = c * app - s * apq, t01 = c * apq - s * aqq;
-          const double t10 = s * app + c * apq, t11 = s * apq + c * aqq;
-          A[p1 * kJacPitch + p1] = t00 * c - t01 * s;
-          A[q1 * kJacPitch + q1] = t10 * s + t11 * c;
-          A[p1 * kJacPitch + q1] = 0.0;
-          A[q1 * kJacPitch + p1] = 0.0;
-        } else {  // rows (p1, q1) x columns (p2, q2), mirrored to the transposed block
-          const double m00 = A[p1 * kJacPitch + p2], m01 = A[p1 * kJacPitch + q2];
-          const double m10 = A[q1 * kJacPitch + p2], m11 = A[q1 * kJacPitch + q2];
-          const double t00 = c1.x * m00 - c1.y * m10, t01 = c1.x * m01 - c1.y * m11;
-          const double t10 = c1.y * m00 + c1.x * m10, t11 = c1.y * m01 + c1.x * m11;
-          const double n00 = t00 * c2.x - t01 * c2.y, n01 = t00 * c2.y + t01 * c2.x;
-          const double n10 = t10 * c2.x - t11 * c2.y, n11 = t10 * c2.y + t11 * c2.x;
-          A[p1 * kJacPitch + p2] = n00;
-          A[p1 * kJacPitch + q2] = n01;
-          A[q1 * kJacPitch + p2] = n10;
-          A[q1 * kJacPitch + q2] = n11;
-          A[p2 * kJacPitch + p1] = n00;
-          A[q2 * kJacPitch + p1] = n01;
-          A[p2 * kJacPitch + q1] = n10;
-          A[q2 * kJacPitch + q1] = n11;
-        }
-      }
-    }
-    __syncthreads();
-    if (!rotated) {  // a sweep without rotations: converged (its identity rounds are not kept)
-      converged = 1;
-      break;
-    }
-    sweeps = sw + 1;
-  }
-  __syncthreads();
-  for (int i = tid; i < kD; i += kJacThreads) diag[(size_t)mtx * kD + i] = A[i * kJacPitch + i];
-  if (tid == 0) {
-    n_rounds[mtx] = sweeps * kJacRounds;
-    info[mtx] = converged ? sweeps + 1 : -1;
-  }
+  // both sides run the same barriers: one at the start and one per round
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x) < 64)
+    jac_lead(sm, Cm, max_sweeps, rot + (size_t)mtx * max_sweeps * kJacRounds * kJacPairs,
+             diag + (size_t)mtx * kD, n_rounds + mtx, info + mtx);
+  else
+    jac_follow(sm, Cm, max_sweeps);
 }
 
 // V = J_1 J_2 ... J_R: each row of V evolves on its own (v <- v J), so one wave
-// per row applies the recorded rounds to its row in LDS; lane k rotates pair k.
-// The rounds' (c, s) are loaded 8 rounds ahead.
+// per row applies the recorded rounds in registers: lane k holds the row's entries
+// of pair k, which move between lanes as in jacobi_kernel.  The rounds' (c, s~) are
+// loaded 16 rounds ahead.  Bound: the dependent chain of a round, 56 ns (two
+// matrices, 14 sweeps: 99 us; 300 us with the row in LDS, indexed).
 constexpr int kVecWaves = 4;
-constexpr int kVecAhead = 8;
+constexpr int kVecAhead = 16;
 
 __global__ __launch_bounds__(kVecWaves * 64) void jacobi_vectors_kernel(
     const double2* __restrict__ rot, const int* __restrict__ n_rounds, int max_sweeps,
     int n_mats, double* __restrict__ V) {
-  __shared__ double vr[kVecWaves][kD];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int grow = blockIdx.x * kVecWaves + w;  // matrix * 128 + row
   if (grow >= n_mats * kD) return;            // whole wave
   const int mtx = grow / kD, row = grow % kD;
-  vr[w][l] = l == row ? 1.0 : 0.0;
-  vr[w][l + 64] = l + 64 == row ? 1.0 : 0.0;
-  const int R = n_rounds[mtx];
-  const double2* rm = rot + (size_t)mtx * max_sweeps * kJacRounds * kJacPairs;
-  double2 buf[kVecAhead];
+  double a = jac_a(l) == row ? 1.0 : 0.0, b = jac_b(l) == row ? 1.0 : 0.0;
+  const int R = __builtin_amdgcn_readfirstlane(n_rounds[mtx]);  // whole sweeps: the pairs end as they begin
+  const double2* rm = rot + (size_t)mtx * max_sweeps * kJacRounds * kJacPairs + l;
+  auto turn = [&](double2 c) {
+    const double na = c.x * a - c.y * b;
+    b = c.y * a + c.x * b;
+    a = na;
+    jac_move(a, b, l);
+  };
+  // whole groups of rounds without branches (the loads past the end repeat the last
+  // round's), so that no wait drains the loads ahead
+  const int whole = R / kVecAhead * kVecAhead;
+  if (whole > 0) {
+    double2 buf[kVecAhead];
 #pragma unroll
-  for (int i = 0; i < kVecAhead; ++i) buf[i] = i < R ? rm[(size_t)i * kJacPairs + l] : make_double2(1.0, 0.0);
-  for (int t0 = 0; t0 < R; t0 += kVecAhead) {
+    for (int i = 0; i < kVecAhead; ++i) buf[i] = rm[(size_t)i * kJacPairs];
+    for (int t0 = 0; t0 < whole; t0 += kVecAhead) {
 #pragma unroll
-    for (int i = 0; i < kVecAhead; ++i) {
-      const int t = t0 + i;
-      if (t < R) {
-        int p, q;
-        round_pair(t % kJacRounds, l, p, q);
+      for (int i = 0; i < kVecAhead; ++i) {
         const double2 c = buf[i];
-        __builtin_amdgcn_wave_barrier();
-        lane_exchange();
-        const double vp = vr[w][p], vq = vr[w][q];
-        vr[w][p] = c.x * vp - c.y * vq;
-        vr[w][q] = c.y * vp + c.x * vq;
-        __builtin_amdgcn_wave_barrier();
-        lane_exchange();
-        const int tn = t + kVecAhead;
-        buf[i] = tn < R ? rm[(size_t)tn * kJacPairs + l] : make_double2(1.0, 0.0);
+        buf[i] = rm[(size_t)min(t0 + kVecAhead + i, R - 1) * kJacPairs];
+        turn(c);
       }
     }
   }
-  __builtin_amdgcn_wave_barrier();
-  lane_exchange();
+  for (int t = whole; t < R; ++t) turn(rm[(size_t)t * kJacPairs]);
   double* vo = V + ((size_t)mtx * kD + row) * kD;
-  vo[l] = vr[w][l];
-  vo[l + 64] = vr[w][l + 64];
+  vo[jac_a(l)] = a;
+  vo[jac_b(l)] = b;
 }
 
 // Sort the eigenpairs by descending eigenvalue (ties: lower index first) and fix
