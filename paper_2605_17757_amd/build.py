@@ -33,6 +33,8 @@ SOURCES = {
     # the two-chunk split instances: the same flags and the max-ilp scheduler
     "decode_mfma_wide2.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm",
                               "-amdgpu-sched-strategy=max-ilp"],
+    # small calls: a team of waves per range
+    "decode_mfma_team.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "bf16_decode.hip": [],
     "mixed.hip": [],
     "calib.hip": ["-ffp-contract=off"],

@@ -1048,7 +1048,7 @@ __device__ __attribute__((always_inline)) inline void walk_pages(uint4* page, co
                                                                  int Hkv, const int32_t* __restrict__ block_table,
                                                                  int max_pages, int b, TokRange R, int kvh, int p0,
                                                                  int p1, int done0, int total, Compute&& compute) {
-  const int l = threadIdx.x;
+  const int l = threadIdx.x & 63;
   const int npg = R.npg;
   const int32_t* __restrict__ bt = block_table + (size_t)b * max_pages + (MIXED ? R.first : 0);
   const uint8_t* __restrict__ base = pages + (size_t)kvh * block_bytes(NG);
@@ -1100,21 +1100,38 @@ __device__ __attribute__((always_inline)) inline void walk_pages(uint4* page, co
 
 }
 
+// Where a piece's partial state goes: slot `piece` of the (sequence, head) rows of
+// the workspace, `stride` slots a row, row0 the slot of the kv-head's first query
+// head.  `last`: the piece ends the sequence, so slots piece + 1 .. num_splits - 1
+// are marked empty.
+struct SlotSink {
+  float* part_o;
+  float* part_ml;
+  size_t row0, stride;
+  int piece, num_splits;
+  bool last;
+  __device__ float* o(int head) const { return part_o + (row0 + head * stride) * kD; }
+  __device__ float* ml(int head) const { return part_ml + (row0 + head * stride) * 2; }
+  __device__ void rest(int head) const {
+    if (!last) return;
+    float* p = ml(head);
+    for (int s2 = piece + 1; s2 < num_splits; ++s2) {
+      p[(s2 - piece) * 2] = -INFINITY;
+      p[(s2 - piece) * 2 + 1] = 0.0f;
+    }
+  }
+};
+
 // Pages [p0, p1) of the token range R of sequence b, kv-head kvh, one chunk of
-// at most 4 query heads: online softmax over the pages and the partial state
-// written to slot `piece` of the (sequence, head) rows, whose slots are
-// row_stride apart.  `last`: the piece ends the range, so slots piece + 1 ..
-// num_splits - 1 are marked empty.
-template <bool MIXED, bool BF, int NG, int NCH>
+// at most 4 query heads: online softmax over the pages, the partial state to `sink`.
+template <bool MIXED, bool BF, int NG, int NCH, class Sink>
 __device__ __attribute__((always_inline)) inline void process_piece(WaveLds<NCH>& L, const uint8_t* __restrict__ pages, int Hkv, int Hq,
                                      const int32_t* __restrict__ block_table, int max_pages, int b,
-                                     TokRange R, int kvh, int p0, int p1, int piece,
-                                     bool last, int num_splits, int row_stride,
-                                     const float* __restrict__ qt,
-                                     float* __restrict__ part_o, float* __restrict__ part_ml,
+                                     TokRange R, int kvh, int p0, int p1,
+                                     const float* __restrict__ qt, const Sink& sink,
                                      int done0, int total) {
   const int g_heads = Hq / Hkv;
-  const int l = threadIdx.x, lo = l & 15, hi = l >> 4;
+  const int l = threadIdx.x & 63, lo = l & 15, hi = l >> 4;
 
   WaveState st[NCH];
   // ---- query operands: q_int = rne(q~ * Q / max|q~|), three int8 digits ----
@@ -1213,12 +1230,8 @@ __device__ __attribute__((always_inline)) inline void process_piece(WaveLds<NCH>
     const float4 zh = *reinterpret_cast<const float4*>(&L.ws[0][4 * hi]);
     const int hout = 4 * chunk + hi;        // head of this lane's accumulators
     if (hout >= g_heads) continue;          // padding head
-    const size_t row = ((size_t)b * Hq + kvh * g_heads + hout) * (MIXED ? row_stride : num_splits) + piece;
-    if (last && lo == 0)  // the range's last piece: the remaining slots hold nothing
-      for (int s2 = piece + 1; s2 < num_splits; ++s2) {
-        part_ml[(row + s2 - piece) * 2] = -INFINITY;
-        part_ml[(row + s2 - piece) * 2 + 1] = 0.0f;
-      }
+    if (lo == 0) sink.rest(hout);
+    float* po = sink.o(hout);
     const bool empty = sc.m == -INFINITY;
     const float cs = lo >= 8 ? 0.25f : 1.0f;  // P.V columns lo >= 8 accumulate 4 x code
 #pragma unroll
@@ -1226,27 +1239,25 @@ __device__ __attribute__((always_inline)) inline void process_piece(WaveLds<NCH>
 #pragma unroll
       for (int F = 0; F < 2; ++F) {
         const int ch = 32 * G + 4 * (lo & 7) + 2 * F + (lo >> 3);
-        part_o[row * kD + ch] = empty ? 0.0f : fmaf(sc.of[2 * G + F], cs, -compf(zh, G * NG / 4));
+        po[ch] = empty ? 0.0f : fmaf(sc.of[2 * G + F], cs, -compf(zh, G * NG / 4));
       }
     }
     if (lo == 0) {
-      part_ml[row * 2] = sc.m;
-      part_ml[row * 2 + 1] = ltot;
+      sink.ml(hout)[0] = sc.m;
+      sink.ml(hout)[1] = ltot;
     }
   }
 }
 
 // The same for 5 to 16 query heads per kv-head (all of them in one wave: scores
 // with one MFMA row per head, P.V in chunks of 4 heads).
-template <bool MIXED, bool BF, int NG, int NCH>
+template <bool MIXED, bool BF, int NG, int NCH, class Sink>
 __device__ __attribute__((always_inline)) inline void process_piece_wide(
     WideLds<NCH>& L, const uint8_t* __restrict__ pages, int Hkv, int Hq, const int32_t* __restrict__ block_table,
-    int max_pages, int b, TokRange R, int kvh, int p0, int p1, int piece, bool last, int num_splits,
-    int row_stride, const float* __restrict__ qt, float* __restrict__ part_o, float* __restrict__ part_ml,
+    int max_pages, int b, TokRange R, int kvh, int p0, int p1, const float* __restrict__ qt, const Sink& sink,
     int done0, int total) {
   const int g_heads = Hq / Hkv;
   const int l = threadIdx.x & 63, lo = l & 15, hi = l >> 4;
-  const size_t stride = MIXED ? row_stride : num_splits;
 
   WideState<NCH> st;
   constexpr int RPH = WideRows<NCH>::RPH, HPL = WideRows<NCH>::HPL, NJ = WideRows<NCH>::NJ;
@@ -1338,14 +1349,9 @@ __device__ __attribute__((always_inline)) inline void process_piece_wide(
     const float ltot = row16_sum(st.lsum[j]);
     const int hh = WideRows<NCH>::lane_head(hi, j);
     if (hh < g_heads && lo == 0) {
-      const size_t row = ((size_t)b * Hq + kvh * g_heads + hh) * stride + piece;
-      part_ml[row * 2] = st.m[j];
-      part_ml[row * 2 + 1] = ltot;
-      if (last)  // the range's last piece: the remaining slots hold nothing
-        for (int s2 = piece + 1; s2 < num_splits; ++s2) {
-          part_ml[(row + s2 - piece) * 2] = -INFINITY;
-          part_ml[(row + s2 - piece) * 2 + 1] = 0.0f;
-        }
+      sink.ml(hh)[0] = st.m[j];
+      sink.ml(hh)[1] = ltot;
+      sink.rest(hh);
     }
   }
   // ---- o~ of head 4c + hi per chunk (sum w z_v per (head, group) through LDS) ----
@@ -1365,13 +1371,13 @@ __device__ __attribute__((always_inline)) inline void process_piece_wide(
     const float4 zh = *reinterpret_cast<const float4*>(&zx[16 * c + 4 * hi]);
     const int hout = 4 * c + hi;
     if (hout >= g_heads) continue;  // padding head
-    const size_t row = ((size_t)b * Hq + kvh * g_heads + hout) * stride + piece;
+    float* po = sink.o(hout);
 #pragma unroll
     for (int G = 0; G < 4; ++G) {
 #pragma unroll
       for (int F = 0; F < 2; ++F) {
         const int ch = 32 * G + 4 * (lo & 7) + 2 * F + (lo >> 3);
-        part_o[row * kD + ch] = empty ? 0.0f : fmaf(st.of[c][2 * G + F], cs, -compf(zh, G * NG / 4));
+        po[ch] = empty ? 0.0f : fmaf(st.of[c][2 * G + F], cs, -compf(zh, G * NG / 4));
       }
     }
   }
@@ -1397,6 +1403,7 @@ using SplitLds = typename std::conditional<NCH == 1, WaveLds<1>, WideLds<NCH>>::
 // wide instances (their query operands, chunk states and prefetched page; at 3
 // waves the prefetched page spills to scratch).
 constexpr int kMinRange = 4;
+constexpr int kTeam = 4;
 template <int NCH>
 struct SplitWaves {
   static constexpr int per_simd = NCH == 1 ? 4 : 2;
@@ -1408,6 +1415,88 @@ __device__ inline int wave_sum_i(int x) {
   return x;
 }
 
+// The INT2 tokens of sequence b: all of them, or with MIXED the history [lo, hi),
+// lo = min(S0, n), hi = max(lo, n - W) (the bf16 sink and recent window are handled
+// elsewhere).  Lengths beyond the block table are clamped.
+template <bool MIXED>
+__device__ inline TokRange int2_range(const int32_t* __restrict__ seq_lens, int b, int max_pages,
+                                      int S0, int W) {
+  const int len = min(max(seq_lens[b], 0), max_pages * kP);
+  if (!MIXED) return tok_range(0, len);
+  const int lo = min(S0, len);
+  return tok_range(lo, max(lo, len - W));
+}
+
+// Pages of a range: [x, xe) of all sequences' pages end to end, the first of them in
+// sequence b, which has npg pages, `before` of the pages lie in earlier sequences
+// (npg == 0: the range is empty).  pw: pages per range.
+struct RangeStart {
+  int64_t x, xe, before, pw;
+  int b, npg;
+};
+template <class Pages>  // pages_of(b): pages of sequence b; called by whole waves
+__device__ inline RangeStart range_start(int r, int n_ranges, int B, int max_pages, int num_splits,
+                                         Pages&& pages_of) {
+  const int l = threadIdx.x & 63;
+  RangeStart s;
+  // pages of the first 64 sequences, and their inclusive prefix sum over the lanes
+  auto scan = [&](int b0, int& np) {
+    const int bb = b0 + l;
+    np = bb < B ? pages_of(bb) : 0;
+    int incl = np;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int y = __shfl_up(incl, off, 64);
+      if (l >= off) incl += y;
+    }
+    return incl;
+  };
+  int np, incl = scan(0, np);
+  int64_t T = __builtin_amdgcn_readlane(incl, 63);
+  for (int b0 = 64; b0 < B; b0 += 64) {
+    const int bb = b0 + l;
+    T += __builtin_amdgcn_readfirstlane(wave_sum_i(bb < B ? pages_of(bb) : 0));
+  }
+  s.pw = max(max((T + n_ranges - 1) / n_ranges,
+                 (int64_t)((max_pages + num_splits - 2) / (num_splits - 1))),
+             (int64_t)kMinRange);
+  s.x = (int64_t)r * s.pw;
+  s.xe = min(T, s.x + s.pw);
+  s.b = s.npg = 0;
+  s.before = 0;
+  if (s.x >= s.xe) return s;
+  for (int b0 = 0;;) {
+    const uint64_t hit = __ballot(b0 + l < B && np > 0 && s.before + (incl - np) <= s.x &&
+                                  s.x < s.before + incl);
+    if (hit) {
+      const int lane = __ffsll((unsigned long long)hit) - 1;
+      s.b = b0 + lane;
+      s.npg = __builtin_amdgcn_readlane(np, lane);
+      s.before += __builtin_amdgcn_readlane(incl - np, lane);
+      return s;
+    }
+    s.before += __builtin_amdgcn_readlane(incl, 63);
+    b0 += 64;
+    if (b0 >= B) return s;  // not reached: page x < T lies in some sequence
+    incl = scan(b0, np);
+  }
+}
+
+// A sequence with no pages gets empty slots from the wave of (range b mod n_ranges,
+// kv-head 0), for all its heads.
+template <class Pages>
+__device__ inline void mark_empty(int r, int n_ranges, int B, int Hq, int num_splits, int stride,
+                                  float* __restrict__ part_ml, Pages&& pages_of) {
+  for (int bb = r; bb < B; bb += n_ranges)
+    if (pages_of(bb) == 0)
+      for (int i = threadIdx.x & 63; i < Hq * num_splits; i += 64) {
+        const size_t row = ((size_t)bb * Hq + i / num_splits) * stride + i % num_splits;
+        part_ml[row * 2] = -INFINITY;
+        part_ml[row * 2 + 1] = 0.0f;
+      }
+}
+
+#ifndef OSCAR_SPLIT_TEAM_UNIT
 template <bool MIXED, bool BF, int NG, int NCH>
 __global__ __launch_bounds__(64) __attribute__((
     amdgpu_waves_per_eu(SplitWaves<NCH>::per_simd, SplitWaves<NCH>::per_simd))) void split_mfma_kernel(
@@ -1419,86 +1508,37 @@ __global__ __launch_bounds__(64) __attribute__((
   const int64_t u = blockIdx.x;
   if (u >= (int64_t)n_ranges * Hkv) return;
   const int r = (int)(u / Hkv), kvh = (int)(u % Hkv);
-  const int l = threadIdx.x;
   const int stride = MIXED ? row_stride : num_splits;
-  // The INT2 tokens of sequence bb: all of them, or with MIXED the history
-  // [lo, hi), lo = min(S0, n), hi = max(lo, n - W) (the bf16 sink and recent
-  // window are handled elsewhere).  Lengths beyond the block table are clamped.
-  auto range_of = [&](int bb) {
-    const int len = min(max(seq_lens[bb], 0), max_pages * kP);
-    if (!MIXED) return tok_range(0, len);
-    const int lo = min(S0, len);
-    return tok_range(lo, max(lo, len - W));
-  };
+  auto range_of = [&](int bb) { return int2_range<MIXED>(seq_lens, bb, max_pages, S0, W); };
+  auto pages_of = [&](int bb) { return range_of(bb).npg; };
   auto run_piece = [&](int bb, TokRange R, int p0, int p1, int piece, bool last, int done0, int total) {
+    const SlotSink sink{part_o, part_ml, ((size_t)bb * Hq + kvh * (Hq / Hkv)) * stride + piece,
+                        (size_t)stride, piece, num_splits, last};
     if constexpr (NCH == 1)
-      process_piece<MIXED, BF, NG, NCH>(L, pages, Hkv, Hq, block_table, max_pages, bb, R, kvh, p0, p1, piece,
-                                        last, num_splits, stride, qt, part_o, part_ml, done0, total);
+      process_piece<MIXED, BF, NG, NCH>(L, pages, Hkv, Hq, block_table, max_pages, bb, R, kvh, p0, p1, qt,
+                                        sink, done0, total);
     else
       process_piece_wide<MIXED, BF, NG, NCH>(L, pages, Hkv, Hq, block_table, max_pages, bb, R, kvh, p0, p1,
-                                             piece, last, num_splits, stride, qt, part_o, part_ml, done0,
-                                             total);
+                                             qt, sink, done0, total);
   };
   if (num_splits == 1) {  // one range per sequence
     const TokRange R = range_of(r);
     run_piece(r, R, 0, R.npg, 0, true, 0, 1 << 20);
     return;
   }
-  // total pages over all sequences
-  int64_t T = 0;
-  for (int b0 = 0; b0 < B; b0 += 64) {
-    const int bb = b0 + l;
-    T += __builtin_amdgcn_readfirstlane(wave_sum_i(bb < B ? range_of(bb).npg : 0));
-  }
-  const int64_t pw = max(max((T + n_ranges - 1) / n_ranges,
-                             (int64_t)((max_pages + num_splits - 2) / (num_splits - 1))),
-                         (int64_t)kMinRange);
-  int64_t x = (int64_t)r * pw;
-  const int64_t xe = min(T, x + pw);
-  // a sequence with no pages gets empty slots from the (range b mod n_ranges,
-  // kv-head 0, chunk 0) wave, for all its heads
-  if (kvh == 0)
-    for (int bb = r; bb < B; bb += n_ranges)
-      if (range_of(bb).npg == 0)
-        for (int i = l; i < Hq * num_splits; i += 64) {
-          const size_t row = ((size_t)bb * Hq + i / num_splits) * stride + i % num_splits;
-          part_ml[row * 2] = -INFINITY;
-          part_ml[row * 2 + 1] = 0.0f;
-        }
-  if (x >= xe) return;
-  // the sequence holding page x: pages before sequence b, scanned 64 sequences at a time
-  int b = 0, npg_b = 0;
-  int64_t before = 0;
-  for (int b0 = 0; b0 < B; b0 += 64) {
-    const int bb = b0 + l;
-    const int np = bb < B ? range_of(bb).npg : 0;
-    int incl = np;  // inclusive prefix sum over the lanes
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(incl, off, 64);
-      if (l >= off) incl += y;
-    }
-    const uint64_t hit =
-        __ballot(bb < B && np > 0 && before + (incl - np) <= x && x < before + incl);
-    if (hit) {
-      const int lane = __ffsll((unsigned long long)hit) - 1;
-      b = b0 + lane;
-      npg_b = __builtin_amdgcn_readlane(np, lane);
-      before += __builtin_amdgcn_readlane(incl - np, lane);
-      break;
-    }
-    before += __builtin_amdgcn_readlane(incl, 63);
-  }
-  if (npg_b == 0) return;  // not reached: page x < T lies in some sequence
-  const int64_t x0 = x;
+  const RangeStart s = range_start(r, n_ranges, B, max_pages, num_splits, pages_of);
+  if (kvh == 0) mark_empty(r, n_ranges, B, Hq, num_splits, stride, part_ml, pages_of);
+  if (s.npg == 0) return;
+  int b = s.b, npg_b = s.npg;
+  int64_t x = s.x, before = s.before;
   __builtin_amdgcn_s_setprio(3);  // lowered in bands as the wave's pages are done
   while (true) {
-    const int64_t end = min(xe, before + npg_b);
-    const int piece = (int)(r - before / pw);
+    const int64_t end = min(s.xe, before + npg_b);
+    const int piece = (int)(r - before / s.pw);
     run_piece(b, range_of(b), (int)(x - before), (int)(end - before), piece, end == before + npg_b,
-              (int)(x - x0), (int)(xe - x0));
+              (int)(x - s.x), (int)(s.xe - s.x));
     x = end;
-    if (x >= xe) break;
+    if (x >= s.xe) break;
     before += npg_b;
     do {  // next sequence with pages
       if (++b >= B) return;  // not reached: pages remain before xe <= T
@@ -1506,20 +1546,142 @@ __global__ __launch_bounds__(64) __attribute__((
     } while (npg_b == 0);
   }
 }
+#else
+// The same ranges with a team of waves per (range, kv-head), for calls too small to
+// give every resident wave a range: the ranges cannot be cut finer (a row has
+// num_splits slots), so the kTeam waves of a workgroup share the pages of each piece evenly, leave their partial states in LDS
+// and merge them as the reduce kernel would, into the piece's one slot.  What a
+// small call waits for is the chain of its pages, one after another (about 1.3 us
+// each).  256 tokens of one sequence, 4/1 heads: 13.0 -> 7.7 us; 8192 tokens, 32/8
+// heads: 14.8 -> 10.8 us.
+template <int NCH>
+struct TeamLds {
+  SplitLds<NCH> wave[kTeam];
+  float ml[kTeam][4 * NCH][2];
+};
+// A wave's o~ rows take the place of its page, or of its weight digits: neither is
+// read again when they are written.
+template <int NCH>
+__device__ inline float (*team_o(SplitLds<NCH>& L))[kD] {
+  if constexpr (NCH == 1) {
+    static_assert(sizeof(L.page) >= 4 * kD * sizeof(float), "room for the o~ rows");
+    return reinterpret_cast<float(*)[kD]>(L.page);
+  } else {
+    static_assert(sizeof(L.wdig) >= 4 * NCH * kD * sizeof(float), "room for the o~ rows");
+    return reinterpret_cast<float(*)[kD]>(L.wdig);
+  }
+}
+struct TeamSink {
+  float (*o_)[kD];
+  float (*ml_)[2];
+  __device__ float* o(int head) const { return o_[head]; }
+  __device__ float* ml(int head) const { return ml_[head]; }
+  __device__ void rest(int) const {}
+};
+
+template <bool MIXED, bool BF, int NG, int NCH>
+__global__ __launch_bounds__(64 * kTeam) __attribute__((
+    amdgpu_waves_per_eu(NCH == 4 ? 1 : SplitWaves<NCH>::per_simd))) void split_team_kernel(
+    const uint8_t* __restrict__ pages, int Hkv, int Hq, const int32_t* __restrict__ block_table,
+    int max_pages, const int32_t* __restrict__ seq_lens, int num_splits, int n_ranges, int B,
+    const float* __restrict__ qt, float* __restrict__ part_o, float* __restrict__ part_ml,
+    int S0, int W, int row_stride) {
+  __shared__ TeamLds<NCH> L;
+  const int r = (int)(blockIdx.x / Hkv), kvh = (int)(blockIdx.x % Hkv);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = Hq / Hkv, stride = MIXED ? row_stride : num_splits;
+  auto range_of = [&](int bb) { return int2_range<MIXED>(seq_lens, bb, max_pages, S0, W); };
+  auto pages_of = [&](int bb) { return range_of(bb).npg; };
+  RangeStart s;
+  if (num_splits == 1) {  // one range per sequence
+    s.b = r;
+    s.npg = pages_of(r);
+    s.x = s.before = 0;
+    s.xe = s.npg;
+    s.pw = 1;
+    if (s.npg == 0) {
+      for (int i = threadIdx.x; i < g; i += blockDim.x) {
+        const size_t row = ((size_t)r * Hq + kvh * g + i) * stride;
+        part_ml[row * 2] = -INFINITY;
+        part_ml[row * 2 + 1] = 0.0f;
+      }
+    }
+  } else {
+    s = range_start(r, n_ranges, B, max_pages, num_splits, pages_of);
+    if (kvh == 0 && w == 0) mark_empty(r, n_ranges, B, Hq, num_splits, stride, part_ml, pages_of);
+  }
+  if (s.npg == 0) return;  // the whole team
+  int b = s.b, npg_b = s.npg;
+  int64_t x = s.x, before = s.before;
+  while (true) {
+    const int64_t end = min(s.xe, before + npg_b);
+    const int piece = num_splits == 1 ? 0 : (int)(r - before / s.pw);
+    const int p0 = (int)(x - before), n = (int)(end - x), per = (n + kTeam - 1) / kTeam;
+    const int w0 = p0 + min(n, w * per), w1 = p0 + min(n, (w + 1) * per);
+    const TeamSink mine{team_o<NCH>(L.wave[w]), L.ml[w]};
+    if constexpr (NCH == 1)
+      process_piece<MIXED, BF, NG, NCH>(L.wave[w], pages, Hkv, Hq, block_table, max_pages, b, range_of(b),
+                                        kvh, w0, w1, qt, mine, 0, 1 << 20);
+    else
+      process_piece_wide<MIXED, BF, NG, NCH>(L.wave[w], pages, Hkv, Hq, block_table, max_pages, b,
+                                             range_of(b), kvh, w0, w1, qt, mine, 0, 1 << 20);
+    __syncthreads();
+    // merge: M = max m_w, sums weighted by 2^(m_w - M); the waves' pages lead
+    const SlotSink out{part_o, part_ml, ((size_t)b * Hq + kvh * g) * stride + piece, (size_t)stride,
+                       piece, num_splits, end == before + npg_b};
+    for (int i = threadIdx.x; i < g * (kD / 4); i += blockDim.x) {
+      const int h = i / (kD / 4), c = i % (kD / 4);
+      float M = -INFINITY;
+      for (int k = 0; k < kTeam; ++k) M = fmaxf(M, L.ml[k][h][0]);
+      float4 o = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      float l = 0.0f;
+      for (int k = 0; k < kTeam; ++k) {
+        const float e = L.ml[k][h][0] == -INFINITY ? 0.0f : exp2f(L.ml[k][h][0] - M);
+        const float4 v = *reinterpret_cast<const float4*>(&team_o<NCH>(L.wave[k])[h][4 * c]);
+        l = fmaf(e, L.ml[k][h][1], l);
+        o.x = fmaf(e, v.x, o.x);
+        o.y = fmaf(e, v.y, o.y);
+        o.z = fmaf(e, v.z, o.z);
+        o.w = fmaf(e, v.w, o.w);
+      }
+      *reinterpret_cast<float4*>(out.o(h) + 4 * c) = o;
+      if (c == 0) {
+        out.ml(h)[0] = M;
+        out.ml(h)[1] = l;
+        out.rest(h);
+      }
+    }
+    x = end;
+    if (x >= s.xe) break;
+    before += npg_b;
+    do {  // next sequence with pages
+      if (++b >= B) return;  // not reached: pages remain before xe <= T
+      npg_b = pages_of(b);
+    } while (npg_b == 0);
+    __syncthreads();  // the merge's reads come before the next piece's states
+  }
+}
+#endif
 
 // The launches of the NCH-chunk instances for the given quantizer format.
 template <int NCH>
 void launch_split_nch(const SplitLaunch& a, bool mixed, int meta_bf16, int ng) {
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)a.blocks), dim3(64), 0, a.stream, a.pages, a.Hkv, a.Hq,
+    hipLaunchKernelGGL(kernel, dim3((unsigned)a.blocks), dim3(64 * a.team), 0, a.stream, a.pages, a.Hkv, a.Hq,
                        a.block_table, a.max_pages, a.seq_lens, a.num_splits, a.ranges, a.B, a.qt,
                        a.part_o, a.part_ml, a.S0, a.W, a.row_stride);
   };
   auto by_ng = [&](auto mixed_c, auto bf_c) {
     constexpr bool M = decltype(mixed_c)::value, BFV = decltype(bf_c)::value;
+#ifdef OSCAR_SPLIT_TEAM_UNIT
+    if (ng == 4) go(split_team_kernel<M, BFV, 4, NCH>);
+    else if (ng == 2) go(split_team_kernel<M, BFV, 2, NCH>);
+    else go(split_team_kernel<M, BFV, 1, NCH>);
+#else
     if (ng == 4) go(split_mfma_kernel<M, BFV, 4, NCH>);
     else if (ng == 2) go(split_mfma_kernel<M, BFV, 2, NCH>);
     else go(split_mfma_kernel<M, BFV, 1, NCH>);
+#endif
   };
   using T = std::true_type;
   using F = std::false_type;
@@ -1534,7 +1696,16 @@ void launch_split_nch(const SplitLaunch& a, bool mixed, int meta_bf16, int ng) {
 
 }  // namespace
 
-#ifdef OSCAR_SPLIT_TWO_CHUNK_UNIT
+#if defined(OSCAR_SPLIT_TEAM_UNIT)
+void launch_split_team(const SplitLaunch& a, bool mixed, int meta_bf16, int ng) {
+  switch (split_chunks(a.Hq / a.Hkv)) {
+    case 1: return launch_split_nch<1>(a, mixed, meta_bf16, ng);
+    case 2: return launch_split_nch<2>(a, mixed, meta_bf16, ng);
+    case 3: return launch_split_nch<3>(a, mixed, meta_bf16, ng);
+    default: return launch_split_nch<4>(a, mixed, meta_bf16, ng);
+  }
+}
+#elif defined(OSCAR_SPLIT_TWO_CHUNK_UNIT)
 void launch_split_two_chunk(const SplitLaunch& a, bool mixed, int meta_bf16, int ng) {
   launch_split_nch<2>(a, mixed, meta_bf16, ng);
 }
@@ -1546,11 +1717,21 @@ hipError_t launch_decode_split_mfma(const uint8_t* pages, int Hkv, int B, int Hq
                                     hipStream_t st, int meta_bf16, int ng,
                                     const MixedSpec* mixed) {
   const int nch = split_chunks(Hq / Hkv);
-  // one range per resident group of Hkv waves
-  const int64_t ranges =
-      num_splits == 1 ? (int64_t)B
-                      : std::max<int64_t>(1, (int64_t)split_waves_per_cu(nch) * cus / Hkv);
+  // one range per resident group of Hkv waves, and no more than the block table can
+  // fill at the least pages of a range (see range_start): the launch of a small call
+  // otherwise consists of waves that find no pages (4096 of them: 3 us)
+  const int64_t resident = (int64_t)split_waves_per_cu(nch) * cus;
+  int64_t ranges = B;
+  if (num_splits > 1) {
+    const int64_t least = std::max<int64_t>(kMinRange, (max_pages + (int64_t)num_splits - 2) / (num_splits - 1));
+    ranges = std::min(std::max<int64_t>(1, resident / Hkv), ((int64_t)B * max_pages + least - 1) / least);
+  }
   const int64_t blocks = ranges * Hkv;
+  // a team of waves per range if the GPU has room for the teams of all ranges, taking
+  // the sequences at half the block table on average (with the teams of the 13-to-16
+  // head instances only one fits a CU's LDS)
+  const int64_t live = std::min(ranges, num_splits > 1 ? (ranges + 1) / 2 : ranges) * Hkv;
+  const int team = live * kTeam <= (nch == 4 ? (int64_t)kTeam * cus : resident) ? kTeam : 1;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   SplitLaunch a;
   a.pages = pages;
@@ -1569,9 +1750,11 @@ hipError_t launch_decode_split_mfma(const uint8_t* pages, int Hkv, int B, int Hq
   a.W = mixed ? mixed->W : 0;
   a.row_stride = mixed ? mixed->row_stride : num_splits;
   a.blocks = blocks;
+  a.team = team;
   a.stream = st;
   const bool mx = mixed != nullptr;
-  if (nch == 1) launch_split_nch<1>(a, mx, meta_bf16, ng);
+  if (team > 1) launch_split_team(a, mx, meta_bf16, ng);
+  else if (nch == 1) launch_split_nch<1>(a, mx, meta_bf16, ng);
   else if (nch == 2) launch_split_two_chunk(a, mx, meta_bf16, ng);
   else if (nch == 3) launch_split_nch<3>(a, mx, meta_bf16, ng);
   else launch_split_nch<4>(a, mx, meta_bf16, ng);
