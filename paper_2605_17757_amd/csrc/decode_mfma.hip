@@ -1427,6 +1427,16 @@ __device__ inline TokRange int2_range(const int32_t* __restrict__ seq_lens, int 
   return tok_range(lo, max(lo, len - W));
 }
 
+// a / b for a >= 0, b > 0; for small calls in 32 bits where both fit (a 64-bit division
+// is some 150 dependent instructions; elsewhere the second path sends 8 bytes of the
+// mixed cache's one-chunk instance to scratch).
+__device__ inline int64_t div64(int64_t a, int64_t b) {
+#ifdef OSCAR_SPLIT_TEAM_UNIT
+  if (((a | b) >> 32) == 0) return (int64_t)((uint32_t)a / (uint32_t)b);
+#endif
+  return a / b;
+}
+
 // Pages of a range: [x, xe) of all sequences' pages end to end, the first of them in
 // sequence b, which has npg pages, `before` of the pages lie in earlier sequences
 // (npg == 0: the range is empty).  pw: pages per range.
@@ -1439,17 +1449,19 @@ __device__ inline RangeStart range_start(int r, int n_ranges, int B, int max_pag
                                          Pages&& pages_of) {
   const int l = threadIdx.x & 63;
   RangeStart s;
-  // pages of the first 64 sequences, and their inclusive prefix sum over the lanes
+  // pages of 64 sequences, and their inclusive prefix sum over the lanes (DPP: shifts
+  // inside rows of 16 lanes, then the rows' last lanes broadcast)
   auto scan = [&](int b0, int& np) {
     const int bb = b0 + l;
     np = bb < B ? pages_of(bb) : 0;
-    int incl = np;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int y = __shfl_up(incl, off, 64);
-      if (l >= off) incl += y;
-    }
-    return incl;
+    int v = np;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
   };
   int np, incl = scan(0, np);
   int64_t T = __builtin_amdgcn_readlane(incl, 63);
@@ -1457,7 +1469,7 @@ __device__ inline RangeStart range_start(int r, int n_ranges, int B, int max_pag
     const int bb = b0 + l;
     T += __builtin_amdgcn_readfirstlane(wave_sum_i(bb < B ? pages_of(bb) : 0));
   }
-  s.pw = max(max((T + n_ranges - 1) / n_ranges,
+  s.pw = max(max(div64(T + n_ranges - 1, n_ranges),
                  (int64_t)((max_pages + num_splits - 2) / (num_splits - 1))),
              (int64_t)kMinRange);
   s.x = (int64_t)r * s.pw;
@@ -1505,9 +1517,7 @@ __global__ __launch_bounds__(64) __attribute__((
     const float* __restrict__ qt, float* __restrict__ part_o, float* __restrict__ part_ml,
     int S0, int W, int row_stride) {
   __shared__ SplitLds<NCH> L;
-  const int64_t u = blockIdx.x;
-  if (u >= (int64_t)n_ranges * Hkv) return;
-  const int r = (int)(u / Hkv), kvh = (int)(u % Hkv);
+  const int r = (int)(blockIdx.x / (uint32_t)Hkv), kvh = (int)(blockIdx.x % (uint32_t)Hkv);
   const int stride = MIXED ? row_stride : num_splits;
   auto range_of = [&](int bb) { return int2_range<MIXED>(seq_lens, bb, max_pages, S0, W); };
   auto pages_of = [&](int bb) { return range_of(bb).npg; };
@@ -1534,7 +1544,7 @@ __global__ __launch_bounds__(64) __attribute__((
   __builtin_amdgcn_s_setprio(3);  // lowered in bands as the wave's pages are done
   while (true) {
     const int64_t end = min(s.xe, before + npg_b);
-    const int piece = (int)(r - before / s.pw);
+    const int piece = (int)(r - div64(before, s.pw));
     run_piece(b, range_of(b), (int)(x - before), (int)(end - before), piece, end == before + npg_b,
               (int)(x - s.x), (int)(s.xe - s.x));
     x = end;
@@ -1581,13 +1591,13 @@ struct TeamSink {
 
 template <bool MIXED, bool BF, int NG, int NCH>
 __global__ __launch_bounds__(64 * kTeam) __attribute__((
-    amdgpu_waves_per_eu(NCH == 4 ? 1 : SplitWaves<NCH>::per_simd))) void split_team_kernel(
+    amdgpu_waves_per_eu(NCH == 4 ? 1 : 2))) void split_team_kernel(
     const uint8_t* __restrict__ pages, int Hkv, int Hq, const int32_t* __restrict__ block_table,
     int max_pages, const int32_t* __restrict__ seq_lens, int num_splits, int n_ranges, int B,
     const float* __restrict__ qt, float* __restrict__ part_o, float* __restrict__ part_ml,
     int S0, int W, int row_stride) {
   __shared__ TeamLds<NCH> L;
-  const int r = (int)(blockIdx.x / Hkv), kvh = (int)(blockIdx.x % Hkv);
+  const int r = (int)(blockIdx.x / (uint32_t)Hkv), kvh = (int)(blockIdx.x % (uint32_t)Hkv);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = Hq / Hkv, stride = MIXED ? row_stride : num_splits;
   auto range_of = [&](int bb) { return int2_range<MIXED>(seq_lens, bb, max_pages, S0, W); };
@@ -1615,7 +1625,7 @@ __global__ __launch_bounds__(64 * kTeam) __attribute__((
   int64_t x = s.x, before = s.before;
   while (true) {
     const int64_t end = min(s.xe, before + npg_b);
-    const int piece = num_splits == 1 ? 0 : (int)(r - before / s.pw);
+    const int piece = num_splits == 1 ? 0 : (int)(r - div64(before, s.pw));
     const int p0 = (int)(x - before), n = (int)(end - x), per = (n + kTeam - 1) / kTeam;
     const int w0 = p0 + min(n, w * per), w1 = p0 + min(n, (w + 1) * per);
     const TeamSink mine{team_o<NCH>(L.wave[w]), L.ml[w]};
@@ -1727,11 +1737,11 @@ hipError_t launch_decode_split_mfma(const uint8_t* pages, int Hkv, int B, int Hq
     ranges = std::min(std::max<int64_t>(1, resident / Hkv), ((int64_t)B * max_pages + least - 1) / least);
   }
   const int64_t blocks = ranges * Hkv;
-  // a team of waves per range if the GPU has room for the teams of all ranges, taking
-  // the sequences at half the block table on average (with the teams of the 13-to-16
-  // head instances only one fits a CU's LDS)
+  // a team of waves per range if the GPU has room for the teams of all ranges (two per
+  // CU; one of the 13-to-16 head instances, by LDS), taking the sequences at half the
+  // block table on average
   const int64_t live = std::min(ranges, num_splits > 1 ? (ranges + 1) / 2 : ranges) * Hkv;
-  const int team = live * kTeam <= (nch == 4 ? (int64_t)kTeam * cus : resident) ? kTeam : 1;
+  const int team = live <= (nch == 4 ? 1 : 2) * (int64_t)cus ? kTeam : 1;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   SplitLaunch a;
   a.pages = pages;
