@@ -341,7 +341,7 @@ int oscar_decode_attn_mixed(const oscar_layout *L, const void *pages, const void
  *                      is first INT2-quantized into the pool at position p - W
  *                      (QuantizeAndWrite of its bf16 row).
  * Then decode attention over the updated cache, exactly oscar_decode_attn_mixed.
- * Four launches: update + query rotation, INT2 split, bf16 partial, merge.  A
+ * Three launches: update + query rotation + bf16 partial, INT2 split, merge.  A
  * sequence with seq_lens[b] = 0 gets no update and a zero output.  Arguments as
  * in oscar_decode_attn_mixed and oscar_kv_append.
  */

@@ -12,7 +12,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "internal.h"
+#include "seg_partial.h"
 
 namespace oscar {
 namespace {
@@ -881,6 +881,39 @@ __global__ __launch_bounds__(kRotWaves * 64) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
+// The prologue of a decode step over the mixed cache, and the bf16 tokens' partial
+// states, which need nothing of it but the newest token (taken from k_new and v_new;
+// the slot that the update overwrites meanwhile is not used).  The partial's blocks
+// come first: they are the longer ones (one wave per 64 slots of a (sequence,
+// kv-head); 5 of the 8 waves at S0 + W = 320).  In a launch of their own between the
+// split kernel and the reduce they took 21.8 us at 64 sequences x 8 KV heads, after a
+// prologue of 14 us, and 10 us after 9 at 8 sequences.
+template <int NH, bool DEF>
+__global__ __launch_bounds__(kRotWaves * 64)
+__attribute__((amdgpu_waves_per_eu(NH > 8 ? 2 : 4, NH > 8 ? 2 : 4))) void mixed_prologue_kernel(
+    uint8_t* __restrict__ pages, StepRows rows, const float* __restrict__ Rk,
+    const float* __restrict__ Rv, float clip_k, float clip_v, QFmt fmt_arg, int append_blocks,
+    const uint16_t* __restrict__ q, int q_rows, int Hq, float qscale, float* __restrict__ qt,
+    SegArgs seg, int seg_blocks) {
+  __shared__ union {
+    RotSmem rot;
+    SegSmem<NH> seg;
+  } sm;
+  int bx = blockIdx.x;
+  if (bx < seg_blocks) {
+    seg_partial_body<NH>(sm.seg, bx, kRotWaves, seg);
+    return;
+  }
+  bx -= seg_blocks;
+  if (bx < 2 * append_blocks) {
+    const int is_v = bx >= append_blocks;
+    append_body(sm.rot, is_v, is_v ? bx - append_blocks : bx, append_blocks, pages, rows, Rk, Rv,
+                clip_k, clip_v, pick(DEF, fmt_arg));
+  } else {
+    prepare_body(bx - 2 * append_blocks, q, q_rows, Rk, qscale, qt, fmt_arg.rph, Hq, rows.Hkv);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Clip calibration (Alg. 1 CalibrateClip).  The paper leaves the procedure open;
 // it is read here as: the candidate ratio whose quantization of the rotated
@@ -1226,9 +1259,29 @@ hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, i
                                       const int32_t* seq_lens, const int32_t* block_table,
                                       int max_pages, const float* Rk, const float* Rv,
                                       float clip_k, float clip_v, QuantFmt fmt, const uint16_t* q,
-                                      int B, int Hq, float qscale, float* qt, hipStream_t st) {
+                                      int B, int Hq, float qscale, float* qt, int num_splits,
+                                      float* part_o, float* part_ml, hipStream_t st) {
   const StepRows rows{k, v, seg, seq_lens, block_table, B, (int)Hkv, max_pages, S0, W};
-  return launch_prologue(pages, rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale, qt, st);
+  const SegArgs sa{seg, k, v, (int)Hkv, S0, W, Hq, seq_lens, max_pages, q, qscale, num_splits,
+                   part_o, part_ml};
+  const int ab = append_blocks(append_items(B, (int)Hkv), (int)Hkv, fmt.rph, device_cus());
+  const int pb = query_blocks(B, Hq, (int)Hkv, fmt.rph, kPrepRows), sb = B * (int)Hkv;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)sb + (unsigned)(2 * ab + pb)), dim3(kRotWaves * 64), 0,
+                       st, static_cast<uint8_t*>(pages), rows, Rk, Rv, clip_k, clip_v, fmt, ab, q,
+                       B * Hq, Hq, qscale, qt, sa, sb);
+  };
+  const int g = Hq / (int)Hkv;
+  if (is_default(fmt)) {
+    if (g <= 4) go(mixed_prologue_kernel<4, true>);
+    else if (g <= 8) go(mixed_prologue_kernel<8, true>);
+    else go(mixed_prologue_kernel<16, true>);
+  } else {
+    if (g <= 4) go(mixed_prologue_kernel<4, false>);
+    else if (g <= 8) go(mixed_prologue_kernel<8, false>);
+    else go(mixed_prologue_kernel<16, false>);
+  }
+  return hipGetLastError();
 }
 
 hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t n_tok,

@@ -110,13 +110,15 @@ hipError_t launch_mixed_append(void* pages, uint16_t* seg, int64_t Hkv, int S0, 
                                const float* Rv, float clip_k, float clip_v, QuantFmt fmt,
                                hipStream_t st);
 // Mixed cache decode-step prologue: one new token per sequence (sink, window with
-// demotion of the oldest window token, or INT2) and the query rotation.
+// demotion of the oldest window token, or INT2), the query rotation, and the bf16
+// tokens' partial states (as launch_seg_partial, the new tokens included).
 hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, int S0, int W,
                                       const uint16_t* k, const uint16_t* v,
                                       const int32_t* seq_lens, const int32_t* block_table,
                                       int max_pages, const float* Rk, const float* Rv,
                                       float clip_k, float clip_v, QuantFmt fmt, const uint16_t* q,
-                                      int B, int Hq, float qscale, float* qt, hipStream_t st);
+                                      int B, int Hq, float qscale, float* qt, int num_splits,
+                                      float* part_o, float* part_ml, hipStream_t st);
 // Partial softmax state of the bf16 tokens (sink and window) of every (sequence,
 // head) row, in the original basis, into slot num_splits of rows of num_splits + 1.
 hipError_t launch_seg_partial(const uint16_t* seg, int Hkv, int S0, int W, int B, int Hq,

@@ -479,12 +479,11 @@ int check_mixed_decode(const oscar_layout* L, const void* pages, const void* seg
   return OSCAR_OK;
 }
 
-// split (history), bf16 partial and merge of a mixed decode; qt already in the workspace
-int launch_mixed_rest(const oscar_layout* L, const void* pages, const void* seg, int32_t S0,
-                      int32_t W, const void* q, int32_t B, int32_t Hq, const int32_t* block_table,
-                      int32_t max_pages_per_seq, const int32_t* seq_lens, const float* R_v,
-                      float sm_scale, int32_t num_splits, void* workspace, void* out,
-                      oscar_dtype out_dtype, hipStream_t hs) {
+// split (history) and merge of a mixed decode; q~ and the bf16 partial already in the workspace
+int launch_mixed_rest(const oscar_layout* L, const void* pages, int32_t S0, int32_t W, int32_t B,
+                      int32_t Hq, const int32_t* block_table, int32_t max_pages_per_seq,
+                      const int32_t* seq_lens, const float* R_v, int32_t num_splits,
+                      void* workspace, void* out, oscar_dtype out_dtype, hipStream_t hs) {
   const DecodeWs ws = decode_ws(B, Hq, (int64_t)num_splits + 1);
   uint8_t* base = static_cast<uint8_t*>(workspace);
   float* po = reinterpret_cast<float*>(base + ws.po_off);
@@ -494,11 +493,6 @@ int launch_mixed_rest(const oscar_layout* L, const void* pages, const void* seg,
                                           Hq, block_table, max_pages_per_seq, seq_lens,
                                           num_splits, reinterpret_cast<const float*>(base + ws.qt_off),
                                           po, pml, hs, meta_bf16(L), groups(L), &mx));
-  if (st) return st;
-  st = hip_status(launch_seg_partial(static_cast<const uint16_t*>(seg), L->num_kv_heads, S0, W, B,
-                                     Hq, seq_lens, max_pages_per_seq,
-                                     static_cast<const uint16_t*>(q), sm_scale * kLog2e,
-                                     num_splits, po, pml, hs));
   if (st) return st;
   return hip_status(launch_decode_reduce(B, Hq, num_splits, po, pml, R_v, out,
                                          out_dtype == OSCAR_OUT_F32 ? 1 : 0, hs, &mx,
@@ -527,8 +521,15 @@ int oscar_decode_attn_mixed(const oscar_layout* L, const void* pages, const void
                                         sm_scale * kLog2e, qt, hs,
                                         L->rot_per_head, L->num_kv_heads));
   if (st) return st;
-  return launch_mixed_rest(L, pages, seg, S0, W, q, B, Hq, block_table, max_pages_per_seq,
-                           seq_lens, R_v, sm_scale, num_splits, workspace, out, out_dtype, hs);
+  uint8_t* base = static_cast<uint8_t*>(workspace);
+  st = hip_status(launch_seg_partial(static_cast<const uint16_t*>(seg), L->num_kv_heads, S0, W, B,
+                                     Hq, seq_lens, max_pages_per_seq,
+                                     static_cast<const uint16_t*>(q), sm_scale * kLog2e, num_splits,
+                                     reinterpret_cast<float*>(base + ws.po_off),
+                                     reinterpret_cast<float*>(base + ws.pml_off), hs));
+  if (st) return st;
+  return launch_mixed_rest(L, pages, S0, W, B, Hq, block_table, max_pages_per_seq, seq_lens, R_v,
+                           num_splits, workspace, out, out_dtype, hs);
 }
 
 int oscar_decode_step_mixed(const oscar_layout* L, void* pages, void* seg, int32_t S0,
@@ -550,15 +551,17 @@ int oscar_decode_step_mixed(const oscar_layout* L, void* pages, void* seg, int32
   if ((int64_t)B * L->num_kv_heads > 0x7fffffffLL) return OSCAR_ERR_UNSUPPORTED;
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const DecodeWs ws = decode_ws(B, Hq, (int64_t)num_splits + 1);
-  float* qt = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + ws.qt_off);
+  uint8_t* base = static_cast<uint8_t*>(workspace);
+  float* qt = reinterpret_cast<float*>(base + ws.qt_off);
   st = hip_status(launch_mixed_step_prologue(
       pages, static_cast<uint16_t*>(seg), L->num_kv_heads, S0, W,
       static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), seq_lens,
       block_table, max_pages_per_seq, R_k, R_v, clip_k, clip_v, quant_fmt(L),
-      static_cast<const uint16_t*>(q), B, Hq, sm_scale * kLog2e, qt, hs));
+      static_cast<const uint16_t*>(q), B, Hq, sm_scale * kLog2e, qt, num_splits,
+      reinterpret_cast<float*>(base + ws.po_off), reinterpret_cast<float*>(base + ws.pml_off), hs));
   if (st) return st;
-  return launch_mixed_rest(L, pages, seg, S0, W, q, B, Hq, block_table, max_pages_per_seq,
-                           seq_lens, R_v, sm_scale, num_splits, workspace, out, out_dtype, hs);
+  return launch_mixed_rest(L, pages, S0, W, B, Hq, block_table, max_pages_per_seq, seq_lens, R_v,
+                           num_splits, workspace, out, out_dtype, hs);
 }
 
 // ---------------------------------------------------------------------------
