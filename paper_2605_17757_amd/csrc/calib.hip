@@ -129,6 +129,7 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const float* __restric
   const int el = threadIdx.x & 31, part = threadIdx.x >> 5;
   const int e = blockIdx.x * 32 + el;  // tile * 1024 + element
   double acc = 0.0;
+#pragma unroll 16
   for (int b = part; b < n_blocks; b += kRedParts)
     acc += (double)partial[((size_t)b * kGramTiles) * 1024 + e];
   sums[part][el] = acc;
@@ -709,33 +710,46 @@ __global__ __launch_bounds__(kVecWaves * 64) void jacobi_vectors_kernel(
 
 // Sort the eigenpairs by descending eigenvalue (ties: lower index first) and fix
 // each eigenvector's sign so that its largest-magnitude entry (the first such)
-// is positive.  One block of 128 threads per matrix; thread i moves column i.
-__global__ __launch_bounds__(kD) void eig_finish_kernel(const double* __restrict__ diag,
+// is positive.  One block of 1024 threads per matrix; thread (column i, part p) looks
+// for the largest of the column's rows 16p .. 16p + 15 (loads issued together) and
+// moves them.  (One thread per column, row after row: 25 us; latency only.)
+constexpr int kFinParts = 8;
+
+__global__ __launch_bounds__(kD * kFinParts) void eig_finish_kernel(const double* __restrict__ diag,
                                                         const double* __restrict__ V,
                                                         double* __restrict__ lam,
                                                         double* __restrict__ U) {
+  constexpr int kRows = kD / kFinParts;
   __shared__ double ls[kD];
-  const int mtx = blockIdx.x, i = threadIdx.x;
+  __shared__ double top[kFinParts][kD];  // a part's largest-magnitude entry, with its sign
+  const int mtx = blockIdx.x, i = threadIdx.x % kD, p = threadIdx.x / kD;
+  const double* Vm = V + (size_t)mtx * kD * kD;
+  double x[kRows];
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) x[r] = Vm[(kRows * p + r) * kD + i];
   const double li = diag[(size_t)mtx * kD + i];
-  ls[i] = li;
+  if (p == 0) ls[i] = li;
+  double best = x[0];
+#pragma unroll
+  for (int r = 1; r < kRows; ++r)
+    if (fabs(x[r]) > fabs(best)) best = x[r];
+  top[p][i] = best;
   __syncthreads();
   int rank = 0;
+#pragma unroll 16
   for (int j = 0; j < kD; ++j) {
     const double lj = ls[j];
     rank += (lj > li || (lj == li && j < i)) ? 1 : 0;
   }
-  lam[(size_t)mtx * kD + rank] = li;
-  const double* Vm = V + (size_t)mtx * kD * kD;
-  double best = -1.0, sgn = 1.0;
-  for (int r = 0; r < kD; ++r) {
-    const double x = Vm[r * kD + i];
-    if (fabs(x) > best) {
-      best = fabs(x);
-      sgn = x < 0.0 ? -1.0 : 1.0;
-    }
-  }
+  if (p == 0) lam[(size_t)mtx * kD + rank] = li;
+  best = top[0][i];
+#pragma unroll
+  for (int k = 1; k < kFinParts; ++k)
+    if (fabs(top[k][i]) > fabs(best)) best = top[k][i];
+  const double sgn = best < 0.0 ? -1.0 : 1.0;
   double* Um = U + (size_t)mtx * kD * kD;
-  for (int r = 0; r < kD; ++r) Um[r * kD + rank] = sgn * Vm[r * kD + i];
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) Um[(kRows * p + r) * kD + rank] = sgn * x[r];
 }
 
 // R = U H_Had P_br: R[i][j] = sum_c U[i][c] H[c][bitrev(j)] (P_br moves column k
@@ -823,7 +837,7 @@ hipError_t launch_eig(const double* C, int n_mats, int max_sweeps, double* diag,
                      dim3(kVecWaves * 64), 0, st, rot, n_rounds, max_sweeps, n_mats, V);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(eig_finish_kernel, dim3((unsigned)n_mats), dim3(kD), 0, st, diag, V, lam, U);
+  hipLaunchKernelGGL(eig_finish_kernel, dim3((unsigned)n_mats), dim3(kD * kFinParts), 0, st, diag, V, lam, U);
   return hipGetLastError();
 }
 
