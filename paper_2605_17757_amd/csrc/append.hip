@@ -7,6 +7,7 @@
 // in fp64 in ascending channel order.  Because each product of a bf16 input and an
 // fp32 matrix entry is exact in fp64, that sum is the same whether it is built of
 // fused or separate operations, bit for bit.
+#include <float.h>
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
@@ -444,6 +445,11 @@ __device__ inline float div_by_scale(float y, float s, float r) {
 // scales (2^-24 <= s; where the residual underflows, |y / s| < 2^-100 and the code
 // follows from the zero point either way), and within these bounds with bfloat16.
 __device__ inline bool fast_scale(float s) { return s >= 0x1p-60f && s <= 0x1p60f; }
+// Clip bound of the values given to div_by_scale: finite, since a residual against an
+// infinite y is NaN.  Finite rows can rotate to an fp32 infinity; a binary16 scale is
+// then saturated, |s| = 65504 >= |z|, and y = +-FLT_MAX has the code of +-infinity.
+// (A bfloat16 scale is past fast_scale's bounds there.)
+__device__ inline float finite_bound(float tau) { return fminf(tau, FLT_MAX); }
 
 // Clip, quantize, pack and write the wave's two rows (half-wave each, lane c of a
 // half: channels 4c .. 4c + 3 in x) to pool slot `slot` (< 0: the row only takes
@@ -468,6 +474,7 @@ __device__ inline void store_rows(uint8_t* __restrict__ pages, int Hkv, int h, i
     for (int e = 0; e < 4; ++e) byte |= quant_code(clamp(x[e], -tau, tau), p) << (2 * e);
   } else {
     const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
+    tau = finite_bound(tau);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float d = div_by_scale(clamp(x[e], -tau, tau), s, r);
@@ -686,6 +693,7 @@ __device__ inline void store_slice32(uint8_t* __restrict__ pages, int Hkv, int h
     }
   } else {
     const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
+    tau = finite_bound(tau);
 #pragma unroll
     for (int jb = 0; jb < 8; ++jb) {
       uint32_t c[4];
@@ -1110,6 +1118,7 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
         }
       } else {
         const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
+        tau = finite_bound(tau);
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
           const float d = div_by_scale(clamp(x[i], -tau, tau), s, r);

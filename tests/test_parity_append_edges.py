@@ -3,8 +3,9 @@ one token, a remainder of 16 tokens, the last size of the one-item-per-block ker
 (256 items of 16 tokens of a head per tensor on a 256-CU GPU) and the first of the
 bulk kernel, one and several KV heads, every quantizer format, tokens that are
 skipped (negative slots), and rows whose quantile, scale or division is degenerate:
-zero, constant, equal magnitudes, one outlier, tiny and huge values.  Page bytes are
-those of the oracle, without exception."""
+zero, constant, equal magnitudes, one outlier, tiny and huge values (saturated scales),
+and finite rows that rotate to an fp32 infinity.  Page bytes are those of the oracle,
+without exception."""
 import numpy as np
 import pytest
 import torch
@@ -52,8 +53,6 @@ def test_append_edges(fmt, n_tok, Hkv):
     R = np.ascontiguousarray(R if rph else R[0])
     Rk, Rv = (R if rk else None), (np.ascontiguousarray(np.swapaxes(R, -1, -2)) if rv else None)
     k, v = _rows(n_tok, Hkv, seed), _rows(n_tok, Hkv, seed + 1)
-    if not meta:  # binary16 scales saturate there: covered by the bf16 formats
-        k, v = k.clamp(-6e4, 6e4), v.clamp(-6e4, 6e4)
     rng = np.random.default_rng(seed)
     slots = rng.permutation(n_pages * 64)[:n_tok].astype(np.int64)
     slots[rng.random(n_tok) < 0.05] = -1
@@ -70,6 +69,48 @@ def test_append_edges(fmt, n_tok, Hkv):
         diff = int((pool.cpu().numpy() != want).sum())
         log(fmt, n_tok, Hkv, rho, "differing bytes", diff)
         assert diff == 0
+
+
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("n_tok,Hkv", [(40, 3), (700, 8)])
+def test_append_overflowing_rows(fmt, n_tok, Hkv):
+    """Finite bf16 rows up to 3.3e38, of which some rotate to infinities of one or both
+    signs (both update kernels): the oracle's page bytes, and its clip errors (finite
+    ones within 1e-9: terms of one sign, some 1e4 of them)."""
+    G, meta, clip_mode, rk, rv, rph = FORMATS[fmt]
+    g = torch.Generator().manual_seed(n_tok)
+    size = torch.tensor([1.0, 1e4, 1e20, 1e36, 1e37, 3e37, 8e37])
+    k, v = (torch.randn(n_tok, Hkv, 128, generator=g).clamp(-4, 4)
+            * size[torch.randint(0, 7, (n_tok, Hkv), generator=g)][..., None] for _ in range(2))
+    k[::9] = k[::9].sign() * 3.3e38
+    v[::9] = 0.0
+    v[::9, :, 7] = 3.3e38
+    k, v = k.to(torch.bfloat16), v.to(torch.bfloat16)
+    assert torch.isfinite(k).all() and torch.isfinite(v).all()
+    R = np.stack([W.rotation(5 + h) for h in range(Hkv if rph else 1)])
+    R = np.ascontiguousarray(R if rph else R[0])
+    Rk, Rv = (R if rk else None), (np.ascontiguousarray(np.swapaxes(R, -1, -2)) if rv else None)
+    dev = [None if m is None else torch.from_numpy(m).cuda() for m in (Rk, Rv)]
+    lay = ok.Layout(Hkv, n_tok // 64 + 1, group_size=G, clip_mode=clip_mode, meta_dtype=meta, rot_per_head=rph)
+    slots = np.arange(n_tok, dtype=np.int64)
+    for rho in (0.5, 0.9, 1.0):
+        pool = torch.full((ok.pool_bytes(lay),), 0x5a, dtype=torch.uint8, device="cuda")
+        ok.kv_append(lay, pool, k.cuda(), v.cuda(), torch.from_numpy(slots).cuda(), dev[0], dev[1], rho, rho)
+        torch.cuda.synchronize()
+        want = np.full(ok.pool_bytes(lay), 0x5a, np.uint8)
+        oracle.kv_append(want, d=128, Hkv=Hkv, P=64, G=G, k=bits(k), v=bits(v), slot_mapping=slots, Rk=Rk,
+                         Rv=Rv, clip_k=rho, clip_v=rho, meta=meta, clip=clip_mode)
+        diff = int((pool.cpu().numpy() != want).sum())
+        log(fmt, n_tok, Hkv, rho, "differing bytes", diff)
+        assert diff == 0
+    cands = np.array([0.31, 0.9, 1.0], np.float32)
+    for x, m, Rx in ((k, dev[0], Rk), (v[:8], dev[1], Rv)):
+        err = ok.calib_clip(lay, x.cuda(), m, torch.from_numpy(cands).cuda())[0].cpu().numpy()
+        ref = oracle.clip_errors(bits(x), Rx, G=G, cands=cands, meta=meta, clip=clip_mode)
+        log(fmt, n_tok, Hkv, "clip errors", err, ref)
+        assert np.array_equal(np.isfinite(err), np.isfinite(ref)) and not np.isnan(err).any()
+        fin = np.isfinite(ref)
+        assert np.all(np.abs(err[fin] - ref[fin]) <= 1e-9 * np.abs(ref[fin]))
 
 
 @pytest.mark.parametrize("fmt", list(FORMATS))
