@@ -45,8 +45,10 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
 //      lo, hi): rows 4hi + i.
 // Bound: latency (the slots' maxima, then their states, then the products).  Few rows
 // are spread over more blocks, with the slots of a row read by more threads at once:
-// 34 slots of 32 rows took three dependent rounds of loads at 8 rows per block of
-// 256 threads (8.3 us; 6.4 us now); 1024 rows 8.1 -> 6.7 us.
+// 40 slots of 64 rows took three dependent rounds of loads at 8 rows per block of
+// 256 threads (10.4 us; 7.1 us now).  Eight slots a round: sixteen, of which a short
+// sequence fills one or two, took 13.8 us instead of 10.4 at 8192 rows of one slot and
+// 93 instead of 58 at 65536.
 // ---------------------------------------------------------------------------
 constexpr int kOmPitch = kD + 4;  // LDS row pitch of o~ (floats)
 
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(int rows, int num_s
   constexpr int kRedRows = RB;
   constexpr int TPR = kRedThreads / RB;  // threads per row in the merge
   constexpr int SG = TPR / 32;           // groups of slots
-  constexpr int SR = RB == 16 ? 16 : 8;  // slots of a group whose loads are issued together
+  constexpr int SR = 8;                  // slots of a group whose loads are issued together
   __shared__ float om[16 * kOmPitch];
   __shared__ float4 og[SG > 1 ? RB * (SG - 1) : 1][kD / 4];  // sums of groups 1..
   __shared__ float mx[kRedThreads / 64][2];                   // per wave: maximum, live slots
@@ -237,8 +239,12 @@ hipError_t launch_decode_reduce(int B, int Hq, int num_splits, const float* part
                                 const float* part_ml, const float* Rv, void* out, int out_f32,
                                 hipStream_t st, const MixedSpec* mixed, int rph, int Hkv) {
   const int rows = B * Hq;
-  // as many rows per block as leave about one block per CU
-  const int rb = rows >= 4096 ? 16 : rows >= 2048 ? 8 : rows >= 512 ? 4 : 2;
+  // As many rows per block as leave a block for every CU, or every other one.  1024 rows
+  // (128 blocks of 8): 7.0 us, 8.0 with 17 slots; 256 blocks of 4: 7.2 to 7.6 and 7.7,
+  // and the split kernel of the next call is slower after them (16 sequences x 4096
+  // tokens, 64/8 heads: 21.6 us, 20.0 after the 128).
+  const int cus = device_cus();
+  const int rb = rows >= 16 * cus ? 16 : rows >= 4 * cus ? 8 : rows >= 2 * cus ? 4 : 2;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(query_blocks(B, Hq, Hkv, rph, rb)), dim3(kRedThreads), 0, st, rows,
                        num_splits, part_o, part_ml, Rv, out, out_f32, rph, Hq, Hkv);

@@ -10,6 +10,7 @@ import pytest
 
 import workloads as W
 from helpers import gpu_append, gpu_decode, log, make_case, max_abs, oracle_append, oracle_decode
+from test_parity_mixed import Mixed
 
 pytestmark = pytest.mark.gpu
 
@@ -38,12 +39,30 @@ def test_team_split(Hq, Hkv, lens):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv", [(1, 3, 3), (73, 7, 7), (64, 8, 8), (89, 23, 23), (64, 32, 8),
-                                      (63, 65, 13), (64, 64, 16), (257, 16, 16)])
+                                      (63, 65, 13), (64, 64, 16), (257, 16, 16),
+                                      (33, 31, 31), (64, 16, 8)])
 def test_reduce_rows(B, Hq, Hkv):
-    """511 / 512, 2047 / 2048, 4095 / 4096 rows and some past them; sampled rows."""
+    """511 / 512, 1023 / 1024, 2047 / 2048, 4095 / 4096 rows and some past them; sampled
+    rows."""
     lens = 1 + (np.arange(B) * 37) % 150
     rng = np.random.default_rng(B)
     pairs = sorted({(0, 0), (B - 1, Hq - 1)} |
                    {(int(rng.integers(B)), int(rng.integers(Hq))) for _ in range(60)})
     _check(W.custom("rows_%d" % (B * Hq), B, Hq, Hkv, lens, seed_index=400 + B, k_outliers=(17,)), (0, 5),
            pairs=pairs)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv", [(16, 32, 8), (33, 31, 31), (16, 64, 8)])
+def test_reduce_rows_mixed(B, Hq, Hkv):
+    """512, 1023 and 1024 rows over the mixed cache, some of them with nine or more
+    pieces beside the bf16 tokens' state."""
+    lens = 1 + (np.arange(B, dtype=np.int32) * 37) % 150
+    lens[[1, B - 1]] = 2300, 2239
+    cfg = W.custom("mixed_rows_%d" % (B * Hq), B, Hq, Hkv, lens, seed_index=450 + B, k_outliers=(17,))
+    m = Mixed(cfg, 20, 50)
+    pool, seg = m.gpu_prefill(lens - 1)
+    got = m.gpu_step(pool, seg, lens, num_splits=12).cpu().numpy()
+    want = m.oracle_decode(*m.oracle_build(lens), lens)
+    err = max_abs(got, want)
+    log(cfg.name, "max |err|", err)
+    assert err <= 2e-4 * max(1.0, float(np.max(np.abs(want))))
