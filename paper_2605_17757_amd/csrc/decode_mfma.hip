@@ -1737,11 +1737,18 @@ hipError_t launch_decode_split_mfma(const uint8_t* pages, int Hkv, int B, int Hq
     ranges = std::min(std::max<int64_t>(1, resident / Hkv), ((int64_t)B * max_pages + least - 1) / least);
   }
   const int64_t blocks = ranges * Hkv;
-  // a team of waves per range if the GPU has room for the teams of all ranges (two per
-  // CU; one of the 13-to-16 head instances, by LDS), taking the sequences at half the
-  // block table on average
-  const int64_t live = std::min(ranges, num_splits > 1 ? (ranges + 1) / 2 : ranges) * Hkv;
-  const int team = live <= (nch == 4 ? 1 : 2) * (int64_t)cus ? kTeam : 1;
+  // A team of waves per range if the teams of all ranges that the block table can fill
+  // are resident at once: two per CU, at 13 to 16 heads per KV head one (LDS), and at up
+  // to 4 heads four, unless the ranges are whole sequences, which may be short.  More
+  // teams than that come in rounds, each of which takes as long as one wave's whole
+  // range if ranges cross sequences (teams merge twice then).  Calls with teams / one
+  // wave per range, 8 KV heads, full tables of the given pages:
+  //   4 heads:  8 x 64 pages (1024 teams) 23.5 / 25.1 us; 8 x 96 (1536), split alone 20.1 / 16.8
+  //   8 heads:  8 x 32 (512) 21.2 / 23.1;  64 x 5 (640) 23.6 / 25.2, but 64 x 6 (768) 33.5 / 27.5
+  //   12 heads: 8 x 32 (512) 23.2 / 26.8;  64 x 6 (768) 44.9 / 37.5
+  //   16 heads: 8 x 16 (256) 20.4 / 27.0;  32 x 6 (384) 34.1 / 30.0
+  const int64_t room = (nch == 4 ? 1 : nch == 1 && num_splits > 1 ? 4 : 2) * (int64_t)cus;
+  const int team = blocks <= room ? kTeam : 1;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   SplitLaunch a;
   a.pages = pages;
