@@ -341,9 +341,11 @@ int oscar_decode_attn_mixed(const oscar_layout *L, const void *pages, const void
  *                      is first INT2-quantized into the pool at position p - W
  *                      (QuantizeAndWrite of its bf16 row).
  * Then decode attention over the updated cache, exactly oscar_decode_attn_mixed.
- * Three launches: update + query rotation + bf16 partial, INT2 split, merge.  A
- * sequence with seq_lens[b] = 0 gets no update and a zero output.  Arguments as
- * in oscar_decode_attn_mixed and oscar_kv_append.
+ * Three launches: update + query rotation + bf16 partial, INT2 split, merge; four,
+ * with the partial apart, past 8 query heads per KV head if S0 + W <= 256 and there
+ * are more (sequence, KV head) pairs than CUs.  A sequence with seq_lens[b] = 0 gets
+ * no update and a zero output.  Arguments as in oscar_decode_attn_mixed and
+ * oscar_kv_append.
  */
 int oscar_decode_step_mixed(const oscar_layout *L, void *pages, void *seg, int32_t S0,
                             int32_t W, const void *k_new, const void *v_new, float clip_k,

@@ -1271,6 +1271,18 @@ hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, i
                                       int B, int Hq, float qscale, float* qt, int num_splits,
                                       float* part_o, float* part_ml, hipStream_t st) {
   const StepRows rows{k, v, seg, seq_lens, block_table, B, (int)Hkv, max_pages, S0, W};
+  // Past 8 heads per KV head a CU holds one block of 8 waves, or two of at most 4.  With
+  // no more than 4 chunks of 64 slots the partial's blocks then run in a launch of their
+  // own, of as many waves as there are chunks, if a CU gets more than one.  A step of
+  // 16/1 heads per KV head, S0 + W = 128, one launch / two: 32 sequences of 8 KV heads 66.4 /
+  // 73.3 us, 48: 104.6 / 102.4, 64: 122.2 / 111.2, 256: 409 / 342; S0 + W = 320: 64
+  // sequences 126.3 / 135.4.  Up to 8 heads one launch is faster at every size.
+  if (Hq / (int)Hkv > 8 && S0 + W <= 4 * kP && (int64_t)B * Hkv > device_cus()) {
+    const hipError_t e = launch_prologue(pages, rows, Rk, Rv, clip_k, clip_v, fmt, q, B, Hq, qscale, qt, st);
+    if (e != hipSuccess) return e;
+    return launch_seg_partial(seg, (int)Hkv, S0, W, B, Hq, seq_lens, max_pages, q, qscale, num_splits,
+                              part_o, part_ml, st);
+  }
   const SegArgs sa{seg, k, v, (int)Hkv, S0, W, Hq, seq_lens, max_pages, q, qscale, num_splits,
                    part_o, part_ml};
   const int ab = append_blocks(append_items(B, (int)Hkv), (int)Hkv, fmt.rph, device_cus());

@@ -3,7 +3,8 @@ arguments while the same launch writes them to the segment store.  With a store 
 unwritten slots hold NaN, for a newest token in the sink, in the window before and
 after it wraps, in no segment (W = 0), and alone: the step's output has the bits of
 decode_attn_mixed on the cache that it leaves behind, repeated steps agree, and the
-written rows are the arguments'."""
+written rows are the arguments'.  The same where the bf16 tokens have a launch of their
+own (more than 8 query heads per KV head, S0 + W <= 256, more pairs than CUs)."""
 import math
 
 import numpy as np
@@ -21,7 +22,18 @@ D = 128
 @pytest.mark.parametrize("Hq,Hkv", [(3, 3), (12, 2), (24, 2)])
 @pytest.mark.parametrize("S0,win", [(64, 256), (0, 64), (48, 0), (5, 3), (20, 600)])
 def test_step_equals_attention_on_its_cache(Hq, Hkv, S0, win):
-    lens = sorted({1, max(1, S0), S0 + 1, S0 + max(1, win), S0 + win + 1, S0 + win + 70, 65, 700})
+    _check(Hq, Hkv, S0, win, sorted({1, max(1, S0), S0 + 1, S0 + max(1, win), S0 + win + 1, S0 + win + 70, 65, 700}))
+
+
+@pytest.mark.parametrize("Hq", [18, 32])
+@pytest.mark.parametrize("S0,win", [(0, 0), (0, 64), (48, 0), (5, 3), (64, 192), (64, 193)])
+def test_many_sequences(Hq, S0, win):
+    Hkv, lens = 2, sorted({1, max(1, S0), S0 + max(1, win), S0 + win + 70, 131})
+    B = torch.cuda.get_device_properties(0).multi_processor_count // Hkv + 2
+    _check(Hq, Hkv, S0, win, [lens[b % len(lens)] for b in range(B)])
+
+
+def _check(Hq, Hkv, S0, win, lens):
     B, mp = len(lens), -(-max(lens) // 64) + 1
     g = torch.Generator().manual_seed(S0 * 1000 + win + Hq)
     lay = ok.Layout(Hkv, B * mp)
