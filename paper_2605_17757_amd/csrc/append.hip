@@ -1216,15 +1216,19 @@ hipError_t launch_prologue(void* pages, const Rows& rows, const float* Rk, const
                            float clip_k, float clip_v, QFmt fmt, const uint16_t* q, int B, int Hq,
                            float qscale, float* qt, hipStream_t st) {
   const int ab = append_blocks(append_items(rows.n_tok, rows.Hkv), rows.Hkv, fmt.rph, device_cus());
-  const int pb = query_blocks(B, Hq, rows.Hkv, fmt.rph, kPrepRows);
+  const int B1 = std::min(B, launch_seqs(Hq));
+  const int pb = query_blocks(B1, Hq, rows.Hkv, fmt.rph, kPrepRows);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)(2 * ab + pb)), dim3(kRotWaves * 64), 0, st,
                        static_cast<uint8_t*>(pages), rows, Rk, Rv, clip_k, clip_v, fmt, ab, q,
-                       B * Hq, Hq, qscale, qt);
+                       B1 * Hq, Hq, qscale, qt);
   };
   if (is_default(fmt)) go(prologue_kernel<Rows, true>);
   else go(prologue_kernel<Rows, false>);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || B1 == B) return e;
+  const size_t o = (size_t)B1 * Hq * kD;  // the other sequences' queries
+  return launch_decode_prepare(q + o, B - B1, Hq, Rk, qscale, qt + o, st, fmt.rph, rows.Hkv);
 }
 }  // namespace
 
@@ -1248,10 +1252,12 @@ hipError_t launch_mixed_append(void* pages, uint16_t* seg, int64_t Hkv, int S0, 
 
 hipError_t launch_decode_prepare(const uint16_t* q, int B, int Hq, const float* Rk,
                                  float qscale, float* qt, hipStream_t st, int rph, int Hkv) {
-  const int rows = B * Hq;
-  hipLaunchKernelGGL(prepare_kernel, dim3(query_blocks(B, Hq, Hkv, rph, kPrepRows)),
-                     dim3(kRotWaves * 64), 0, st, q, rows, Rk, qscale, qt, rph, Hq, Hkv);
-  return hipGetLastError();
+  return by_seqs(B, launch_seqs(Hq), [&](int b0, int nb) {
+    const size_t o = (size_t)b0 * Hq * kD;
+    hipLaunchKernelGGL(prepare_kernel, dim3(query_blocks(nb, Hq, Hkv, rph, kPrepRows)),
+                       dim3(kRotWaves * 64), 0, st, q + o, nb * Hq, Rk, qscale, qt + o, rph, Hq, Hkv);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_step_prologue(void* pages, int64_t Hkv, const uint16_t* k, const uint16_t* v,
@@ -1270,6 +1276,14 @@ hipError_t launch_mixed_step_prologue(void* pages, uint16_t* seg, int64_t Hkv, i
                                       float clip_k, float clip_v, QuantFmt fmt, const uint16_t* q,
                                       int B, int Hq, float qscale, float* qt, int num_splits,
                                       float* part_o, float* part_ml, hipStream_t st) {
+  if (const int most = launch_seqs(Hq); B > most)
+    return by_seqs(B, most, [&](int b0, int nb) {
+      const size_t kv = (size_t)b0 * Hkv * kD, row = (size_t)b0 * Hq, part = row * (num_splits + 1);
+      return launch_mixed_step_prologue(
+          pages, seg ? seg + kv * 2 * (S0 + W) : nullptr, Hkv, S0, W, k + kv, v + kv, seq_lens + b0,
+          block_table + (size_t)b0 * max_pages, max_pages, Rk, Rv, clip_k, clip_v, fmt, q + row * kD,
+          nb, Hq, qscale, qt + row * kD, num_splits, part_o + part * kD, part_ml + part * 2, st);
+    });
   const StepRows rows{k, v, seg, seq_lens, block_table, B, (int)Hkv, max_pages, S0, W};
   // Past 8 heads per KV head a CU holds one block of 8 waves, or two of at most 4.  With
   // no more than 4 chunks of 64 slots the partial's blocks then run in a launch of their

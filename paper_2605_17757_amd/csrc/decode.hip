@@ -230,14 +230,25 @@ hipError_t launch_decode_split(const uint8_t* pages, int Hkv, int B, int Hq,
                                const int32_t* seq_lens, int num_splits, const float* qt,
                                float* part_o, float* part_ml, hipStream_t st, int meta_bf16,
                                int ng, const MixedSpec* mixed) {
-  return launch_decode_split_mfma(pages, Hkv, B, Hq, block_table, max_pages, seq_lens,
-                                  num_splits, device_cus(), qt, part_o, part_ml, st,
-                                  meta_bf16, ng, mixed);
+  // (with more splits the grid does not grow with the sequences)
+  return by_seqs(B, num_splits == 1 ? launch_seqs(Hq) : B, [&](int b0, int nb) {
+    const size_t row = (size_t)b0 * Hq, part = row * (mixed ? mixed->row_stride : num_splits);
+    return launch_decode_split_mfma(pages, Hkv, nb, Hq, block_table + (size_t)b0 * max_pages, max_pages,
+                                    seq_lens + b0, num_splits, device_cus(), qt + row * kD,
+                                    part_o + part * kD, part_ml + part * 2, st, meta_bf16, ng, mixed);
+  });
 }
 
 hipError_t launch_decode_reduce(int B, int Hq, int num_splits, const float* part_o,
                                 const float* part_ml, const float* Rv, void* out, int out_f32,
                                 hipStream_t st, const MixedSpec* mixed, int rph, int Hkv) {
+  if (const int most = launch_seqs(Hq); B > most)
+    return by_seqs(B, most, [&](int b0, int nb) {
+      const size_t row = (size_t)b0 * Hq, part = row * (mixed ? num_splits + 1 : num_splits);
+      return launch_decode_reduce(nb, Hq, num_splits, part_o + part * kD, part_ml + part * 2, Rv,
+                                  static_cast<char*>(out) + row * kD * (out_f32 ? 4 : 2), out_f32, st,
+                                  mixed, rph, Hkv);
+    });
   const int rows = B * Hq;
   // As many rows per block as leave a block for every CU, or every other one.  1024 rows
   // (128 blocks of 8): 7.0 us, 8.0 with 17 slots; 256 blocks of 4: 7.2 to 7.6 and 7.7,

@@ -162,6 +162,20 @@ void launch_split_two_chunk(const SplitLaunch& a, bool mixed, int meta_bf16, int
 // Instances with more than one wave per range (decode_mfma_team.hip).
 void launch_split_team(const SplitLaunch& a, bool mixed, int meta_bf16, int ng);
 int device_cus();  // compute units of the current device (cached)
+
+// A launch holds fewer than 2^32 threads; with more, the grid is cut without an error.
+// Launches whose grid grows with the (sequence, head) rows take at most launch_seqs
+// sequences, 2^20 rows (at most a block of 512 threads each), and the rest in further
+// launches.
+inline int launch_seqs(int Hq) { return Hq >= 1 << 20 ? 1 : (1 << 20) / Hq; }
+template <class Launch>  // launch(b0, n): sequences b0 .. b0 + n - 1
+hipError_t by_seqs(int B, int most, Launch&& launch) {
+  for (int b0 = 0; b0 < B; b0 += most) {
+    const hipError_t e = launch(b0, B - b0 < most ? B - b0 : most);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 // mixed != nullptr: rows of num_splits + 1 slots, the last one in the original
 // basis (added after the back-rotation).
 hipError_t launch_decode_reduce(int B, int Hq, int num_splits, const float* part_o,

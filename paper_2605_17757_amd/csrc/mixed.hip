@@ -19,10 +19,14 @@ hipError_t launch_seg_nh(const uint16_t* seg, int Hkv, int S0, int W, int B, int
                          const int32_t* seq_lens, int max_pages, const uint16_t* q, float qscale,
                          int num_splits, float* part_o, float* part_ml, hipStream_t st) {
   const int nw = std::min(kSegWaves, std::max(1, (S0 + W + kP - 1) / kP));
-  const SegArgs args{seg, nullptr, nullptr, Hkv, S0, W, Hq, seq_lens, max_pages, q, qscale,
-                     num_splits, part_o, part_ml};
-  hipLaunchKernelGGL(seg_partial_kernel<NH>, dim3((unsigned)(B * Hkv)), dim3(64 * nw), 0, st, args);
-  return hipGetLastError();
+  return by_seqs(B, launch_seqs(Hq), [&](int b0, int nb) {
+    const size_t row = (size_t)b0 * Hq, part = row * (num_splits + 1);
+    const SegArgs args{seg ? seg + (size_t)b0 * Hkv * 2 * (S0 + W) * kD : nullptr, nullptr, nullptr, Hkv,
+                       S0, W, Hq, seq_lens + b0, max_pages, q + row * kD, qscale, num_splits,
+                       part_o + part * kD, part_ml + part * 2};
+    hipLaunchKernelGGL(seg_partial_kernel<NH>, dim3((unsigned)(nb * Hkv)), dim3(64 * nw), 0, st, args);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace
