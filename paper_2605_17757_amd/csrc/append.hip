@@ -1330,10 +1330,11 @@ hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t 
     jobs.err[i] = tensors[i].err;
     jobs.best[i] = tensors[i].best;
   }
-  // one block per CU over all tensors, and no more than the workspace has room for
-  const int nb = std::min(append_blocks(append_items((int)n_tok, Hkv), Hkv, fmt.rph,
-                                        device_cus() / n_tensors),
-                          clip_blocks(n_tok * Hkv, Hkv, fmt.rph));
+  // one block per CU over all tensors, and no more than each has room for
+  int64_t room = append_blocks(append_items((int)n_tok, Hkv), Hkv, fmt.rph, device_cus() / n_tensors);
+  for (int i = 0; i < n_tensors; ++i) room = std::min(room, tensors[i].blocks);
+  const int nb = (int)(fmt.rph ? room / Hkv * Hkv : room);
+  if (nb < 1) return hipErrorInvalidValue;
   hipLaunchKernelGGL(clip_err_kernel, dim3((unsigned)nb, (unsigned)n_tensors), dim3(kClipWaves * 64),
                      0, st, jobs, (int)n_tok, cands, n_cands, fmt, Hkv);
   hipError_t e = hipGetLastError();
@@ -1343,7 +1344,6 @@ hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t 
   return hipGetLastError();
 }
 
-// Blocks that a tensor's partial errors have room for in the workspace.
 int clip_blocks(int64_t n_rows, int Hkv, int rph) {
   const int64_t heads = rph ? Hkv : 1;  // rph: blocks per head, times Hkv
   const int64_t items = (n_rows / heads + 3) / 4;

@@ -215,15 +215,18 @@ hipError_t launch_eig(const double* C, int n_mats, int max_sweeps, double* diag,
 hipError_t launch_compose(const double* U, int n_mats, double* R64, float* R32, hipStream_t st);
 // Mean squared quantization error of the rotated rows x [n_tok][Hkv][128] of each
 // tensor (at most two) for each candidate clip ratio (n_cands <= 32) and the first
-// minimizing candidate; with fmt.rph, R is [Hkv][128][128].  partial:
-// clip_blocks(n_tok * Hkv, Hkv, rph) x n_cands doubles of its own per tensor.
+// minimizing candidate; with fmt.rph, R is [Hkv][128][128].  partial: room for the sums
+// of at most `blocks` blocks, n_cands doubles each, of its own per tensor; the launch
+// takes no more blocks than that (with fmt.rph at least Hkv are needed).
 struct ClipTensor {
   const uint16_t* x;
   const float* R;
   double* partial;
+  int64_t blocks;
   double* err;
   float* best;
 };
+// Blocks that the workspace reserves room for.
 int clip_blocks(int64_t n_rows, int Hkv, int rph);
 hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t n_tok,
                               const float* cands, int n_cands, QuantFmt fmt, int Hkv,

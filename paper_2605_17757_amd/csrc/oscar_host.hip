@@ -843,7 +843,8 @@ int oscar_calib_clip(const oscar_layout* L, const void* x, int64_t n_tok, const 
   const int64_t rows = n_tok * L->num_kv_heads;
   if (workspace_bytes < clip_ws_bytes(rows, L->num_kv_heads, n_cands))
     return OSCAR_ERR_WORKSPACE_TOO_SMALL;
-  const ClipTensor job{static_cast<const uint16_t*>(x), R, static_cast<double*>(workspace), err, best};
+  const ClipTensor job{static_cast<const uint16_t*>(x), R, static_cast<double*>(workspace),
+                       clip_blocks(rows, L->num_kv_heads, L->rot_per_head), err, best};
   return hip_status(launch_clip_errors(&job, 1, n_tok, cands, n_cands, quant_fmt(L),
                                        L->num_kv_heads, static_cast<hipStream_t>(stream)));
 }
@@ -894,12 +895,12 @@ int oscar_calibrate_layer(const oscar_layout* L, const void* q, const void* k, c
   if (launch_compose(U, hm, nullptr, R_k, s) != hipSuccess) return OSCAR_ERR_HIP;
   if (launch_compose(U + hm * dd, hm, nullptr, R_v, s) != hipSuccess) return OSCAR_ERR_HIP;
   // K and V together.  V's partial sums take the place of the attention rows and
-  // second-moment tiles, which are no longer needed: at least 40 KB + 512 B per KV
-  // head, where at most max(128, Hkv) blocks of at most 32 sums are launched per tensor.
-  double* part = reinterpret_cast<double*>(ws + w.clip_off);
+  // second-moment tiles, which are no longer needed.
   const ClipTensor jobs[2] = {
-      {static_cast<const uint16_t*>(k), R_k, part, err, clip},
-      {static_cast<const uint16_t*>(v), R_v, reinterpret_cast<double*>(cw), err + n_cands, clip + 1}};
+      {static_cast<const uint16_t*>(k), R_k, reinterpret_cast<double*>(ws + w.clip_off),
+       clip_blocks(T * Hkv, Hkv, L->rot_per_head), err, clip},
+      {static_cast<const uint16_t*>(v), R_v, reinterpret_cast<double*>(cw),
+       (int64_t)(calib_ws(T, Hq).total / (n_cands * sizeof(double))), err + n_cands, clip + 1}};
   if (launch_clip_errors(jobs, 2, T, cands, n_cands, quant_fmt(L), Hkv, s) != hipSuccess)
     return OSCAR_ERR_HIP;
   return OSCAR_OK;

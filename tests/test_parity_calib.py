@@ -310,3 +310,24 @@ def test_calibrate_layer_one_rotation_per_kv_head():
         log("  per-head clip %.2f (oracle on the GPU's R: %.2f)" % (float(c), cands_np[np.argmin(ref)]))
         if srt[1] - srt[0] > 1e-9 * srt[0]:
             assert float(c) == float(cands_np[np.argmin(ref)])
+
+
+@pytest.mark.parametrize("T,Hkv,rph", [(1, 1, 0), (3, 200, 0), (2, 140, 1)])
+def test_calibrate_layer_few_tokens_many_heads(T, Hkv, rph):
+    """The smallest scratch beside the most partial clip errors (32 candidates): both
+    tensors' ratios are those of calib_clip on the returned rotations, and nothing is
+    written past the workspace."""
+    q, k, v = (x.cuda() for x in _acts(T, Hkv, Hkv, 660 + Hkv))
+    lay = ok.Layout(num_kv_heads=Hkv, num_pages=1, rot_per_head=rph)
+    cands = torch.linspace(0.69, 1.0, 32, dtype=torch.float32, device="cuda")
+    n = ok.calibrate_layer_workspace_bytes(lay, T, Hkv, 32)
+    ws = torch.full((n + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    cal = ok.calibrate_layer(lay, q, k, v, cands, workspace=ws[:n])
+    torch.cuda.synchronize()
+    assert bool((ws[n:] == 0x5a).all())
+    for x, R, c in ((k, cal["R_K"], cal["clip"][0]), (v, cal["R_V"], cal["clip"][1])):
+        err, best = ok.calib_clip(lay, x, R, cands)
+        low = torch.sort(err).values
+        log("T", T, "heads", Hkv, "ratio", float(c), "alone", float(best[0]))
+        if float(low[1] - low[0]) > 1e-12 * float(low[0]):  # sums in another order
+            assert float(c) == float(best[0])
