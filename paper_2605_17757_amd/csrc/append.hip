@@ -82,9 +82,10 @@ __device__ inline uint32_t quant_code(float y, const QParams& p) {
 
 // Token-wise clip threshold (App. "Scale Determination and Per-token Clipping
 // Details"): the rho-quantile of |x~| over the row, a_k + f (a_{k+1} - a_k) with
-// pos = rho (d - 1), k = floor(pos), f = pos - k, in fp32 steps.
+// pos = rho (d - 1), k = floor(pos), f = pos - k, in fp32 steps.  (Candidate ratios are
+// read on the device, unchecked: those below 0 are taken as 0, so that k is an index.)
 __device__ inline void quantile_pos(float rho, int& k, float& f) {
-  const float pos = __fmul_rn(rho, (float)(kD - 1));
+  const float pos = fmaxf(__fmul_rn(rho, (float)(kD - 1)), 0.0f);
   k = min((int)floorf(pos), kD - 1);
   f = __fsub_rn(pos, (float)k);
 }

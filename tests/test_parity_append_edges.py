@@ -137,3 +137,17 @@ def test_clip_errors_edges(fmt, n_tok, Hkv, n_cands):
     log(fmt, n_tok, Hkv, "max error over mean square", float(np.max(np.abs(got - want))) / max(ms, 1e-300))
     assert np.all(np.abs(got - want) <= 1e-12 * ms)
     assert float(best.cpu()[0]) == float(cands[int(np.argmin(got))])
+
+
+@pytest.mark.parametrize("fmt", ["paper", "g64_quantile_identity_v"])
+def test_clip_ratios_outside_the_unit_interval(fmt):
+    """Candidate ratios are not validated: one below 0 gives the error of 0, one above 1
+    that of 1, and the others are not affected."""
+    G, meta, clip_mode, _, _, rph = FORMATS[fmt]
+    lay = ok.Layout(2, 1, group_size=G, clip_mode=clip_mode, meta_dtype=meta, rot_per_head=rph)
+    x = torch.randn(40, 2, 128, generator=torch.Generator().manual_seed(9)).to(torch.bfloat16).cuda()
+    R = torch.from_numpy(W.rotation(9)).cuda()
+    err = [ok.calib_clip(lay, x, R, torch.tensor(c, device="cuda"))[0].cpu().tolist()
+           for c in ([0.0, 0.5, 1.0], [-0.01, 0.5, 1.5], [-3.0, 0.5, 2.0])]
+    log(fmt, err)
+    assert err[0] == err[1] == err[2]
