@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
   const uint16_t* __restrict__ x_all = jobs.x[blockIdx.y];
   const float* __restrict__ R = jobs.R[blockIdx.y];
   const int bx = blockIdx.x, gx = gridDim.x;
-  const int t = threadIdx.x, w = t >> 6, l = t & 63, kq = l >> 4, j = l & 15;
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, kq = l >> 4, j = l & 15;
   if (R) stage_rot<kClipWaves>(Rs, R + (fmt.rph ? (size_t)(bx % Hkv) * kD * kD : 0), t);  // gx: a multiple of Hkv
   __syncthreads();
   uint32_t* area = area_all[w];
@@ -1034,7 +1034,11 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
   const int rr = l >> 2, q = l & 3;
   double mine = 0.0;  // lane n: the wave's error of candidate n
   auto clamp = [](float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); };
-  for (int n = w; n < n_mine; n += kClipWaves) {
+  // One or two items: `share` waves take the same item and every share-th candidate (the
+  // sums have the same terms in the same order), at most a wave per SIMD, whose products
+  // would wait for each other.
+  const int share = n_mine == 1 ? 4 : n_mine == 2 ? 2 : 1;
+  for (int n = w / share; n < n_mine; n += kClipWaves / share) {
     const int item = bx + n * gx, tok0 = item / Hkv * kItemRows, h = item % Hkv;
     const uint16_t* src = x_all + ((size_t)tok0 * Hkv + h) * kD;
     uint32_t row[kItemRows];
@@ -1096,7 +1100,7 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
 #pragma unroll
     for (int i = 0; i < 32; ++i) x64[i] = (double)x[i];
 #pragma unroll 1
-    for (int n_c = 0; n_c < n_cands; ++n_c) {
+    for (int n_c = w % share; n_c < n_cands; n_c += share) {
       const float clip = cands[n_c];
       float tau;
       if (fmt.quantile) {
