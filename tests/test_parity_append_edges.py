@@ -151,3 +151,62 @@ def test_clip_ratios_outside_the_unit_interval(fmt):
            for c in ([0.0, 0.5, 1.0], [-0.01, 0.5, 1.5], [-3.0, 0.5, 2.0])]
     log(fmt, err)
     assert err[0] == err[1] == err[2]
+
+
+@pytest.mark.parametrize("fmt,Hkv", [("default", 8), ("paper", 8), ("bf16_per_head", 6)])
+def test_step_with_more_items_than_blocks(fmt, Hkv):
+    """A decode step's update takes its items of 16 tokens of a head on at most one block
+    per CU and tensor (per-head rotations: a multiple of the heads); with more items a
+    block takes several in turn.  Page bytes: the oracle's for decode_step; for
+    decode_step_mixed those of kv_append of the rows that leave the window, and the
+    segment store changes in the new tokens' rows only."""
+    G, meta, clip_mode, rk, rv, rph = FORMATS[fmt]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    B = 16 * (cus // Hkv) + 16 * 2 + 5
+    assert -(-B // 16) * Hkv > cus
+    lay = ok.Layout(Hkv, B, group_size=G, clip_mode=clip_mode, meta_dtype=meta, rot_per_head=rph)
+    R = np.stack([W.rotation(70 + h) for h in range(Hkv if rph else 1)])
+    R = np.ascontiguousarray(R if rph else R[0])
+    Rd = torch.from_numpy(R).cuda()
+    rng = np.random.default_rng(B)
+    k, v = _rows(B, Hkv, 71), _rows(B, Hkv, 72)
+    q = torch.randn(B, Hkv, 128, generator=torch.Generator().manual_seed(73)).to(torch.bfloat16).cuda()
+    table = torch.from_numpy(rng.permutation(B).astype(np.int32)).reshape(B, 1).cuda()
+    lens = torch.from_numpy(rng.integers(1, 65, size=B).astype(np.int32)).cuda()
+    out = torch.empty(B, Hkv, 128, device="cuda")
+    slots = table[:, 0].long() * 64 + lens.long() - 1
+    slots[5::17] = -1  # skipped tokens
+    pool = ok.alloc_pool(lay)
+    ok.decode_step(lay, pool, k.cuda(), v.cuda(), slots, 0.9, 0.9, q, table, lens, Rd, Rd, 128 ** -0.5, 1,
+                   ok.alloc_workspace(lay, B, Hkv, 1), out)
+    torch.cuda.synchronize()
+    want, keep = np.zeros(ok.pool_bytes(lay), np.uint8), (slots >= 0).cpu()
+    oracle.kv_append(want, d=128, Hkv=Hkv, P=64, G=G, k=bits(k[keep]), v=bits(v[keep]),
+                     slot_mapping=slots.cpu().numpy()[keep.numpy()], Rk=R, Rv=R, clip_k=0.9, clip_v=0.9, meta=meta,
+                     clip=clip_mode)
+    diff = int((pool.cpu().numpy() != want).sum())
+    log(fmt, "step: differing bytes", diff)
+    assert diff == 0
+
+    S0, win = 2, 3
+    lens = lens % 9 + 1
+    store = torch.stack([_rows(B * (S0 + win), Hkv, s).reshape(B, S0 + win, Hkv, 128).transpose(1, 2) for s in (74, 75)], 2)
+    seg = store.contiguous().cuda()
+    pool.zero_()
+    ok.decode_step_mixed(lay, pool, seg, S0, win, k.cuda(), v.cuda(), 0.9, 0.9, q, table, lens, Rd, Rd, 128 ** -0.5, 1,
+                         ok.alloc_mixed_workspace(lay, B, Hkv, 1), out)
+    p = lens.long().cpu() - 1
+    slot = torch.where(p < S0, p, S0 + (p - S0) % win)
+    b = torch.arange(B)
+    left = store[b, :, :, slot]  # [B, Hkv, 2, 128]: what the new rows displaced
+    demoted = p - win >= S0
+    ref = ok.alloc_pool(lay)
+    to = table[:, 0].long() * 64 + (lens.long() - 1 - win)
+    ok.kv_append(lay, ref, *(left[demoted][:, :, i].contiguous().cuda() for i in (0, 1)), to[demoted.cuda()].contiguous(),
+                 Rd, Rd, 0.9, 0.9)
+    torch.cuda.synchronize()
+    store = store.clone()
+    store[b, :, 0, slot], store[b, :, 1, slot] = k, v
+    same = bool((pool == ref).all()), bool((seg.cpu().view(torch.int16) == store.contiguous().view(torch.int16)).all())
+    log(fmt, "mixed step: demoted", int(demoted.sum()), "pages, segments as expected", same)
+    assert demoted.any() and same == (True, True)
