@@ -436,8 +436,8 @@ __device__ inline float token_quantile2(const float (&x)[4], float rmax, float r
 // y / s for a group's stored scale s (at most 11 significant bits), correctly
 // rounded as an IEEE division, in three operations from r = 1 / s rounded to
 // nearest: one residual correction of y r.  Equal to y / s for every pair of an
-// 11-bit and a 24-bit significand (2^33 cases enumerated), as long as r and the
-// residual are not subnormal; see fast_scale.
+// 11-bit and a 24-bit significand (all 2^33: tests/test_scale_division.py), as long as r
+// and the residual are not subnormal; see fast_scale.
 __device__ inline float div_by_scale(float y, float s, float r) {
   const float q = __fmul_rn(y, r);
   return __fmaf_rn(__fmaf_rn(-q, s, y), r, q);

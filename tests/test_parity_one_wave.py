@@ -4,7 +4,8 @@ to 4, 8, 12 and 16 query heads per KV head (with padding heads), groups of 32, 6
 three.  Calls with enough ranges that teams of waves do not fit the GPU: short ragged
 sequences of 16 KV heads, zero-length ones among them, and ranges that cross
 sequences.  The oracle decodes sampled rows from the same page bytes; outputs within
-2e-4 of the largest: operands of 21 bits, fp32 sums of some hundred terms."""
+2e-4 of the largest: operands of 21 bits, fp32 sums of some hundred terms.  The bf16
+output is the rounded fp32 output."""
 import numpy as np
 import pytest
 import torch
@@ -74,3 +75,11 @@ def test_one_wave_instances(G, meta, g, mixed):
         err = float(np.max(np.abs(np.stack([got[b, h] for b, h in pairs]) - want)))
         log("G", G, "meta", meta, "g", g, "mixed", mixed, "splits", S, "max |err|", err)
         assert np.isfinite(got).all() and err <= tol
+        out16 = torch.empty(B, Hq, D, device="cuda", dtype=torch.bfloat16)
+        args = (q.cuda(), table_d, lens_d, Rk_d, Rv_d, D ** -0.5, S)
+        if mixed:
+            ok.decode_attn_mixed(lay, pool, seg, S0, WIN, *args, ok.alloc_mixed_workspace(lay, B, Hq, S), out16)
+        else:
+            ok.decode_attn(lay, pool, *args, ok.alloc_workspace(lay, B, Hq, S), out16)
+        torch.cuda.synchronize()
+        assert torch.equal(out16, out.to(torch.bfloat16))

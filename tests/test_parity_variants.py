@@ -114,7 +114,8 @@ def _small_cfg(name, seed):
 
 @pytest.mark.parametrize("variant", list(VARIANTS))
 def test_variant_append_and_decode_small(variant):
-    """Ragged lengths, one row per wave (the small-append kernel), 1/3/default splits."""
+    """Ragged lengths, up to 44 items of 16 tokens (the one-item-per-block cache update),
+    1/3/default splits."""
     vc = VCase(_small_cfg("var_" + variant, 230 + list(VARIANTS).index(variant)), variant)
     lens = vc.cfg.lens
     log("variant", variant, "lens", list(lens))
@@ -155,11 +156,11 @@ def test_variant_gqa_wide(variant, g):
 
 @pytest.mark.parametrize("variant", ["bf16_meta", "g64", "g128", "identity_v", "per_head_r"])
 def test_bf16_output_is_rne_of_fp32_every_instance(variant):
-    """For every split-kernel instance (1 to 16 query heads per KV head: one chunk,
-    the two-row and the one-row-per-head score tiles; each group size and metadata
-    format) and both reduce instances (8 and 16 rows per block), with 1 and 3
-    splits, the bf16 output is the round-to-nearest-even of the fp32 output of the
-    same call: the two differ only in the final store."""
+    """The bf16 output is the round-to-nearest-even of the fp32 output of the same call
+    (the two differ only in the final store), with 1 and 3 splits, for every number
+    of chunks of query heads per KV head in these formats on the team instances of
+    the split kernel (small calls; test_parity_one_wave.py checks the same for those
+    with one wave per range), and for reduce blocks of 2 and of 16 rows."""
     for g in (1, 4, 6, 8, 12, 16):
         cfg = W.custom("rne_g%d_%s" % (g, variant), 3, 2 * g, 2, [5, 130, 300],
                        seed_index=300 + g + list(VARIANTS).index(variant))
@@ -183,8 +184,7 @@ def test_bf16_output_is_rne_of_fp32_every_instance(variant):
                                      "identity_kv_paper_format", "per_head_r",
                                      "per_head_paper_format"])
 def test_variant_bulk_append_qwen3_4b_shape(variant):
-    """8192 tokens x 8 KV heads: the bulk cache update (two rows per wave, the
-    quantile searched per wave half)."""
+    """8192 tokens x 8 KV heads: the bulk cache update (16-token items, one per wave)."""
     cfg = W.config(1)
     vc = VCase(cfg, variant)
     lens = cfg.lens
