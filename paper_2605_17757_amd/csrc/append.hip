@@ -1017,6 +1017,8 @@ struct ClipJobs {
   float* best[2];
 };
 
+// FEW: blocks have at most two items each, see `share`.
+template <bool FEW>
 __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
     ClipJobs jobs, int n_tok, const float* __restrict__ cands, int n_cands, QFmt fmt, int Hkv) {
   __shared__ float4 Rs[kD][kD / 4];                                   // 64 KB
@@ -1025,7 +1027,7 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
   const uint16_t* __restrict__ x_all = jobs.x[blockIdx.y];
   const float* __restrict__ R = jobs.R[blockIdx.y];
   const int bx = blockIdx.x, gx = gridDim.x;
-  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63, kq = l >> 4, j = l & 15;
+  const int t = threadIdx.x, w = t >> 6, l = t & 63, kq = l >> 4, j = l & 15;
   if (R) stage_rot<kClipWaves>(Rs, R + (fmt.rph ? (size_t)(bx % Hkv) * kD * kD : 0), t);  // gx: a multiple of Hkv
   __syncthreads();
   uint32_t* area = area_all[w];
@@ -1036,8 +1038,9 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
   auto clamp = [](float v, float lo, float hi) { return __builtin_amdgcn_fmed3f(v, lo, hi); };
   // One or two items: `share` waves take the same item and every share-th candidate (the
   // sums have the same terms in the same order), at most a wave per SIMD, whose products
-  // would wait for each other.
-  const int share = n_mine == 1 ? 4 : n_mine == 2 ? 2 : 1;
+  // would wait for each other.  300 tokens of one head: 37.9 -> 23.0 us.
+  const int share = !FEW ? 1 : n_mine == 1 ? 4 : 2;
+  const int first = !FEW ? 0 : __builtin_amdgcn_readfirstlane(w % share);
   for (int n = w / share; n < n_mine; n += kClipWaves / share) {
     const int item = bx + n * gx, tok0 = item / Hkv * kItemRows, h = item % Hkv;
     const uint16_t* src = x_all + ((size_t)tok0 * Hkv + h) * kD;
@@ -1096,11 +1099,11 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
       lane_exchange();
     }
     const bool live = tok0 + rr < n_tok;
-    double x64[32];
+    double x64[32];  // (an infinite one has an infinite error whatever its code: no finite_bound)
 #pragma unroll
     for (int i = 0; i < 32; ++i) x64[i] = (double)x[i];
 #pragma unroll 1
-    for (int n_c = w % share; n_c < n_cands; n_c += share) {
+    for (int n_c = first; n_c < n_cands; n_c += share) {
       const float clip = cands[n_c];
       float tau;
       if (fmt.quantile) {
@@ -1123,7 +1126,6 @@ __global__ __launch_bounds__(kClipWaves * 64) void clip_err_kernel(
         }
       } else {
         const float s = p.deg ? 1.0f : p.sf, r = p.deg ? 0.0f : __fdiv_rn(1.0f, p.sf);  // deg: y / s = 0
-        tau = finite_bound(tau);
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
           const float d = div_by_scale(clamp(x[i], -tau, tau), s, r);
@@ -1340,8 +1342,10 @@ hipError_t launch_clip_errors(const ClipTensor* tensors, int n_tensors, int64_t 
   for (int i = 0; i < n_tensors; ++i) room = std::min(room, tensors[i].blocks);
   const int nb = (int)(fmt.rph ? room / Hkv * Hkv : room);
   if (nb < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(clip_err_kernel, dim3((unsigned)nb, (unsigned)n_tensors), dim3(kClipWaves * 64),
-                     0, st, jobs, (int)n_tok, cands, n_cands, fmt, Hkv);
+  const bool few = append_items((int)n_tok, Hkv) <= 2 * (int64_t)nb;
+  hipLaunchKernelGGL(few ? clip_err_kernel<true> : clip_err_kernel<false>,
+                     dim3((unsigned)nb, (unsigned)n_tensors), dim3(kClipWaves * 64), 0, st, jobs,
+                     (int)n_tok, cands, n_cands, fmt, Hkv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(clip_reduce_kernel, dim3((unsigned)n_tensors), dim3(kClipParts * kMaxClipCands),
