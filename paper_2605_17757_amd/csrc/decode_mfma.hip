@@ -1559,11 +1559,11 @@ __global__ __launch_bounds__(64) __attribute__((
 #else
 // The same ranges with a team of waves per (range, kv-head), for calls too small to
 // give every resident wave a range: the ranges cannot be cut finer (a row has
-// num_splits slots), so the kTeam waves of a workgroup share the pages of each piece evenly, leave their partial states in LDS
-// and merge them as the reduce kernel would, into the piece's one slot.  What a
-// small call waits for is the chain of its pages, one after another (about 1.3 us
-// each).  256 tokens of one sequence, 4/1 heads: 13.0 -> 7.7 us; 8192 tokens, 32/8
-// heads: 14.8 -> 10.8 us.
+// num_splits slots), so the kTeam waves of a workgroup share the pages of each piece
+// evenly, leave their partial states in LDS and merge them as the reduce kernel would,
+// into the piece's one slot.  What a small call waits for is the chain of its pages, one
+// after another (about 1.3 us each).  256 tokens of one sequence, 4/1 heads: 13.0 -> 7.5
+// us; 8192 tokens, 32/8 heads: 14.8 -> 10.2 us.
 template <int NCH>
 struct TeamLds {
   SplitLds<NCH> wave[kTeam];

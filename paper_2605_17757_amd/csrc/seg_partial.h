@@ -8,11 +8,11 @@
 // sink is full, and it fills its slots from S0 upward before wrapping.  Softmax
 // sums do not depend on the order of the tokens, so the kernel walks the slots.
 //
-// seg_partial_body: one block per (sequence, kv-head) with one wave per 64-slot chunk
-// (nw = ceil((S0 + W) / 64) waves, at most 8; wave w takes the chunks w, w + nw,
-// ...); up to 5 waves a block (S0 + W <= 320) and 8 query heads per kv-head,
-// two blocks are resident per CU (<= 128 VGPRs, <= 80 KB LDS), so every wave of
-// the launch runs at once.
+// seg_partial_body: one block of nw waves per (sequence, kv-head), one wave per 64-slot
+// chunk (wave w takes the chunks w, w + nw, ...).  In a launch of their own nw =
+// ceil((S0 + W) / 64), at most 8; in the launch of a step's prologue blocks have 8 waves,
+// and those without a chunk only take part in the merge.  Two blocks are resident per CU
+// at up to 8 query heads per kv-head (<= 128 VGPRs, <= 80 KB LDS).
 //   loads  : K with 16-byte loads, 8 lanes per 128-byte half row (loads 0-7 of a
 //            lane: channel half 0 of rows 8 i + lane / 8; loads 8-15: half 1),
 //            issued with the V dwords of the chunk's first 32 tokens (4 heads;
