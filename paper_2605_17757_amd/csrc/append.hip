@@ -576,10 +576,12 @@ __device__ inline void append_body(RotSmem& sm, int is_v, int bx, int gx,
 // reads of the fp32 R in LDS, and x~ goes through the wave's 4 KB area one channel
 // half at a time.
 //
-// Bound: the fp64 matrix core, 16,384 of a SIMD's cycles per item.  With four waves
-// per SIMD at different points of their items, the rest of an item (about 1,100
-// VALU instructions, 2,100 with the token quantile, and the dependent loads that
-// route its rows) runs while other waves' products do.  The quantizer has the most
+// Bound: the fp64 matrix core, 16,384 of a SIMD's cycles per item: 74 % busy over a
+// prompt of 131072 tokens, 37 % where a wave has 1.6 items in the token-quantile format.
+// With four waves per SIMD at different points of their items, the rest of an item (980
+// vector instructions beside its 256 products, 2,570 with the token quantile, and the
+// dependent loads that route its rows) runs while other waves' products do.  At the 128
+// registers of 16 waves the instances keep 12 to 44 bytes per lane in scratch.  The quantizer has the most
 // work per lane here (32 channels), which costs the fewest instructions; 32 lanes a
 // row, as in store_rows, took 1,700 and 7,000.  131072 tokens x 8 heads: 1474 us with
 // two waves per SIMD, IEEE divisions per code and the routing loads in front of each
@@ -937,8 +939,8 @@ __attribute__((amdgpu_waves_per_eu(NH > 8 ? 2 : 4, NH > 8 ? 2 : 4))) void mixed_
 // a_{k+1}.  Sums are added in a fixed order: over the lanes per item and candidate
 // (lane n keeps candidate n), then the waves, then (clip_reduce_kernel) the blocks.
 //
-// Bound: VALU issue, about 11 instructions per channel and candidate (four of them
-// fp64).  One wave per row, with cross-lane reductions, three divisions per value and
+// Bound: VALU issue, 67 % busy at two waves per SIMD, the matrix cores 22 %: 12,500
+// instructions per item with 21 candidates, its sort and 256 products among them.  One wave per row, with cross-lane reductions, three divisions per value and
 // the group's parameters formed by every lane for every candidate, took 1112 us per
 // tensor (8878 tokens x 8 heads, 21 candidates, groups of 128 with the quantile).
 // ---------------------------------------------------------------------------

@@ -405,10 +405,11 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_kernel(
 // entry comes from within a pair, which therefore never leaves the lane.
 // Rotations are kept as (c, s~), s~ = s if a < b, -s otherwise: a' = c a - s~ b and
 // b' = s~ a + c b are then the two rows of J^T, in either order.  They are recorded
-// for jacobi_vectors_kernel.  Bound: LDS and fp64 VALU of the updates, 0.86 us of a
-// round alone, the rotations 0.43 us; 1670 us for two matrices of 14 and 10 sweeps
-// (the whole matrix in index order, with the rotations formed between two barriers:
-// 2.0 us a round, 3593 us).
+// for jacobi_vectors_kernel.  Bound: the chain of a round, 0.95 us of LDS accesses and
+// fp64 VALU work of 16 waves (1,250 and 340 instructions; VALU 48 % busy on the block's
+// CU, 40 % of the waves' time at waits and the barrier); 1700 us for two matrices of 14
+// and 10 sweeps (the whole matrix in index order, with the rotations formed between two
+// barriers: 2.0 us a round, 3593 us).
 // ---------------------------------------------------------------------------
 constexpr int kJacRounds = kD - 1;
 constexpr int kJacPairs = kD / 2;
