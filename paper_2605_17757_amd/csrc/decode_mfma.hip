@@ -1563,7 +1563,7 @@ __global__ __launch_bounds__(64) __attribute__((
 // evenly, leave their partial states in LDS and merge them as the reduce kernel would,
 // into the piece's one slot.  What a small call waits for is the chain of its pages, one
 // after another (about 1.3 us each).  256 tokens of one sequence, 4/1 heads: 13.0 -> 7.5
-// us; 8192 tokens, 32/8 heads: 14.8 -> 10.2 us.
+// us; 8192 tokens, 32/8 heads: 14.8 -> 10.8 us.
 template <int NCH>
 struct TeamLds {
   SplitLds<NCH> wave[kTeam];
